@@ -67,6 +67,31 @@ inline hipError_t launch_kernel(void (*k)(Params...), dim3 grid, dim3 block, hip
 // once per (device, kernel, size) and remembered; `fallback` if the runtime cannot say.
 uint32_t cached_occupancy(const void* kernel, int threads, uint32_t fallback);
 
+// GELU u * Phi(u), Phi(u) = erfc(-u / sqrt 2) / 2, by one formula for every u: with x = |u| / sqrt 2,
+// erfc(x) exp(x^2) = 1 - s P(s), s = p x / (1 + p x), P of degree 8 fitted (iteratively reweighted least
+// squares, float64) to 8e-9 relative; the lower half of Phi then keeps its RELATIVE accuracy where
+// 1 + erff cancels.  In float32, 4M points against float64: worst error 1.4e-7 relative for u > 0 (1.3e-7 with
+// erff) and 2.4e-7 absolute overall (4.5e-7), mean for |u| < 3 8.5e-9 (1.1e-8).
+// 21 instructions and two transcendentals without a branch; erff runs both of its branches in nearly
+// every wavefront, which bound the bias + GELU row kernel (16384 x 1024 bf16: 51 us, 1.3 TB/s).
+__device__ __forceinline__ float gelu_erf(float u)
+{
+    const float w = fminf(fabsf(u), 40.0f) * 0.261629509039022f;           // p / sqrt 2, p = 0.37; Phi is 0 or 1 long before 40
+    const float s = w * __builtin_amdgcn_rcpf(w + 1.0f);
+    float q = 0.06571311780777805f;
+    q = fmaf(q, s, -0.2684981873662216f);
+    q = fmaf(q, s, 0.31317405139724813f);
+    q = fmaf(q, s, 0.14699449755866215f);
+    q = fmaf(q, s, -0.34761325419640404f);
+    q = fmaf(q, s, -0.9969110527035865f);
+    q = fmaf(q, s, 3.292456271732396f);
+    q = fmaf(q, s, -4.254981375949771f);
+    q = fmaf(q, s, 3.049674549243907f);
+    q = fmaf(q, -s, 1.0f);
+    const float h = q * __builtin_amdgcn_exp2f(fmaf(u * u, -0.72134752044448170368f, -1.0f));   // erfc(x) / 2
+    return u * (u >= 0.0f ? 1.0f - h : h);
+}
+
 inline bool aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15u) == 0; }
 
 } // namespace lithos

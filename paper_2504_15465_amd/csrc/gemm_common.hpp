@@ -47,11 +47,6 @@ __device__ __forceinline__ uint16_t f32_to_bf16_rne(float f)
     return (uint16_t)(u >> 16);
 }
 
-__device__ __forceinline__ float gelu_erf(float u)
-{
-    return 0.5f * u * (1.0f + erff(u * 0.70710678118654752440f));
-}
-
 // Compile-time loop: the body sees its index as a constant, so register
 // arrays indexed with it never become memory.
 template <typename F, int... Is>

@@ -89,31 +89,94 @@ __device__ __forceinline__ float row_max(float v, float* red)
     return v;
 }
 
-__device__ __forceinline__ float gelu_erf_f(float u)
+// W consecutive elements of a row or of a flat tensor, 16 bytes (or as close as W comes) at a time
+template <bool F32, int W>
+__device__ __forceinline__ void load_run(const void* p, int64_t i, float (&v)[W])
 {
-    return 0.5f * u * (1.0f + erff(u * 0.70710678118654752440f));
+    if constexpr (W == 1) {
+        v[0] = load_elem<F32>(p, i);
+    } else if constexpr (F32) {
+#pragma unroll
+        for (int q = 0; q < W / 4; ++q) {
+            const float4 f = reinterpret_cast<const float4*>(reinterpret_cast<const float*>(p) + i)[q];
+            v[4 * q] = f.x; v[4 * q + 1] = f.y; v[4 * q + 2] = f.z; v[4 * q + 3] = f.w;
+        }
+    } else {
+        const uint16_t* h = reinterpret_cast<const uint16_t*>(p) + i;
+        uint32_t u[W / 2];
+        if constexpr (W == 8) { const uint4 t = *reinterpret_cast<const uint4*>(h); u[0] = t.x; u[1] = t.y; u[2] = t.z; u[3] = t.w; }
+        else { const uint2 t = *reinterpret_cast<const uint2*>(h); u[0] = t.x; u[1] = t.y; }
+#pragma unroll
+        for (int q = 0; q < W / 2; ++q) { v[2 * q] = __uint_as_float(u[q] << 16); v[2 * q + 1] = __uint_as_float(u[q] & 0xffff0000u); }
+    }
+}
+
+template <bool F32, int W>
+__device__ __forceinline__ void store_run(void* p, int64_t i, const float (&v)[W])
+{
+    if constexpr (W == 1) {
+        store_elem<F32>(p, i, v[0]);
+    } else if constexpr (F32) {
+#pragma unroll
+        for (int q = 0; q < W / 4; ++q)
+            reinterpret_cast<float4*>(reinterpret_cast<float*>(p) + i)[q] = make_float4(v[4 * q], v[4 * q + 1], v[4 * q + 2], v[4 * q + 3]);
+    } else {
+        uint32_t u[W / 2];
+#pragma unroll
+        for (int q = 0; q < W / 2; ++q) u[q] = f32_to_bf16_bits(v[2 * q]) | ((uint32_t)f32_to_bf16_bits(v[2 * q + 1]) << 16);
+        uint16_t* h = reinterpret_cast<uint16_t*>(p) + i;
+        if constexpr (W == 8) *reinterpret_cast<uint4*>(h) = make_uint4(u[0], u[1], u[2], u[3]);
+        else *reinterpret_cast<uint2*>(h) = make_uint2(u[0], u[1]);
+    }
+}
+
+// the elements' bf16 rounding, and what it dropped (the second plane of a split-bf16 tensor)
+template <int W>
+__device__ __forceinline__ void drop_rounded(float (&v)[W])
+{
+#pragma unroll
+    for (int e = 0; e < W; ++e) v[e] -= bf16_bits_to_f32(f32_to_bf16_bits(v[e]));
 }
 
 // ---- y = act(x + bias): 2048 consecutive elements per block ---------------
-template <bool IN32, bool OUT32>
+// W = 8: a thread owns eight consecutive elements of one row (cols % 8 == 0, aligned operands): 16-byte
+// accesses, one column index per thread.  W = 1: any sizes; a thread's elements are 256 apart and its column
+// index is stepped, not divided for.  Bound by HBM once neither a 64-bit remainder per element nor erff is
+// in the way (16384 x 1024 bf16: bias + GELU, LayerNorm and softmax in a row 119 -> 61 us, of which the
+// bias + GELU 51 us before and the softmax 52).
+template <bool IN32, bool OUT32, int W>
 __global__ __launch_bounds__(256) void bias_act_kernel(RowArgs a, AtomArgs atom)
 {
     const uint32_t L = atom_logical_block(atom);
     const int64_t total = a.rows * a.cols;
-    const int64_t base = (int64_t)L * 2048;
+    const int64_t base = (int64_t)L * 2048 + threadIdx.x * W;
+    const uint32_t cols = (uint32_t)a.cols;
+    uint32_t c = total >> 32 ? (uint32_t)(base % a.cols) : (uint32_t)base % cols;
+    const uint32_t step = (256 * W) % cols;
+    float v[8 / W][W];
 #pragma unroll
-    for (int i = 0; i < 8; ++i) {
-        int64_t idx = base + threadIdx.x + i * 256;
-        if (idx < total) {
-            float v = load_elem<IN32>(a.x, idx);
-            if (a.flags & LITHOS_F_BIAS) v += a.p0[idx % a.cols];
-            if (a.flags & LITHOS_F_GELU) v = gelu_erf_f(v);
-            store_elem<OUT32>(a.y, idx, v);
-            if (!OUT32 && (a.flags & LITHOS_F_OUT_SPLIT)) {      // lo plane follows the hi plane
-                float hi = bf16_bits_to_f32(f32_to_bf16_bits(v));
-                reinterpret_cast<uint16_t*>(a.y)[total + idx] = f32_to_bf16_bits(v - hi);
-            }
+    for (int i = 0; i < 8 / W; ++i)
+        if (base + i * 256 * W < total) load_run<IN32>(a.x, base + i * 256 * W, v[i]);
+#pragma unroll
+    for (int i = 0; i < 8 / W; ++i) {
+        const int64_t idx = base + i * 256 * W;
+        if (idx >= total) break;
+        if (a.flags & LITHOS_F_BIAS) {
+            float b[W];
+            load_run<true>(a.p0, c, b);
+#pragma unroll
+            for (int e = 0; e < W; ++e) v[i][e] += b[e];
         }
+        if (a.flags & LITHOS_F_GELU)
+#pragma unroll
+            for (int e = 0; e < W; ++e) v[i][e] = gelu_erf(v[i][e]);
+        store_run<OUT32>(a.y, idx, v[i]);
+        if (!OUT32 && (a.flags & LITHOS_F_OUT_SPLIT)) {      // lo plane follows the hi plane
+            drop_rounded(v[i]);
+            store_run<false>(a.y, total + idx, v[i]);
+        }
+        c += step;
+        if (c >= cols) c -= cols;
     }
 }
 
@@ -152,7 +215,7 @@ __global__ __launch_bounds__(256) void sum_slices_kernel(RowArgs a, AtomArgs ato
 #pragma unroll
         for (int t = 0; t < W; ++t) {
             if (a.flags & LITHOS_F_BIAS) v[t] += a.p0[c + t];
-            if (a.flags & LITHOS_F_GELU) v[t] = gelu_erf_f(v[t]);
+            if (a.flags & LITHOS_F_GELU) v[t] = gelu_erf(v[t]);
             if (a.flags & LITHOS_F_RESIDUAL) v[t] += a.p1[r * ldr + c + t];
         }
         if constexpr (VEC && OUT32) {
@@ -217,78 +280,60 @@ __global__ __launch_bounds__(256) void layernorm_kernel(RowArgs a, AtomArgs atom
     }
 }
 
-// Register-resident variant: the row is read ONCE with 16-byte (fp32) or
-// 8-byte (bf16) loads, four elements per thread and step, and stays in
-// registers for the mean, the centred variance and the output.  Needs
-// H % 4 == 0 and H <= 16 * TPR.
-template <bool IN32, bool OUT32, int TPR>
+// Register-resident variant: the row is read ONCE and stays in registers (16 elements per thread) for the
+// mean, the centred variance and the output; needs H <= 16 * TPR.  A thread holds 16 / W runs of W
+// consecutive elements: W = 4 or 8 where H and the pointers permit 16-byte accesses of fp32 or bf16 rows,
+// W = 1 for any H.  Bound by HBM on many rows (16384 x 1024 bf16: 17 us = 4.0 TB/s), by launch and
+// latency on few.
+template <bool IN32, bool OUT32, int TPR, int W>
 __global__ __launch_bounds__(256) void layernorm_vec_kernel(RowArgs a, AtomArgs atom)
 {
     __shared__ float red[4];
-    constexpr int NV = 4;                                   // 4-element groups per thread
+    constexpr int NV = 16 / W;
     const uint32_t L = atom_logical_block(atom);
     constexpr int RPB = 256 / TPR;
     const int64_t row = (int64_t)L * RPB + threadIdx.x / TPR;
     const int t = threadIdx.x % TPR;
     const bool live = row < a.rows;
-    const int64_t H = a.cols, off = row * H;
-    float v[NV][4];
+    const int H = (int)a.cols;
+    const int64_t off = row * H;
+    float v[NV][W];
     float s = 0.0f;
 #pragma unroll
     for (int j = 0; j < NV; ++j) {
-        const int64_t c = 4 * (t + (int64_t)j * TPR);
-        v[j][0] = v[j][1] = v[j][2] = v[j][3] = 0.0f;
-        if (live && c < H) {
-            if constexpr (IN32) {
-                const float4 f = *reinterpret_cast<const float4*>(reinterpret_cast<const float*>(a.x) + off + c);
-                v[j][0] = f.x; v[j][1] = f.y; v[j][2] = f.z; v[j][3] = f.w;
-            } else {
-                const uint2 u = *reinterpret_cast<const uint2*>(reinterpret_cast<const uint16_t*>(a.x) + off + c);
-                v[j][0] = __uint_as_float(u.x << 16); v[j][1] = __uint_as_float(u.x & 0xffff0000u);
-                v[j][2] = __uint_as_float(u.y << 16); v[j][3] = __uint_as_float(u.y & 0xffff0000u);
-            }
-            s += (v[j][0] + v[j][1]) + (v[j][2] + v[j][3]);
-        }
+        const int c = W * (t + j * TPR);
+#pragma unroll
+        for (int e = 0; e < W; ++e) v[j][e] = 0.0f;
+        if (live && c < H) load_run<IN32>(a.x, off + c, v[j]);
     }
+#pragma unroll
+    for (int j = 0; j < NV; ++j)
+#pragma unroll
+        for (int e = 0; e < W; ++e) s += v[j][e];
     const float mean = row_sum<TPR>(s, red) / (float)H;
     float q = 0.0f;
 #pragma unroll
-    for (int j = 0; j < NV; ++j) {
-        const int64_t c = 4 * (t + (int64_t)j * TPR);
-        if (live && c < H)
+    for (int j = 0; j < NV; ++j)
+        if (live && W * (t + j * TPR) < H)
 #pragma unroll
-            for (int e = 0; e < 4; ++e) { const float d = v[j][e] - mean; q += d * d; }
-    }
+            for (int e = 0; e < W; ++e) { const float d = v[j][e] - mean; q += d * d; }
     const float var = row_sum<TPR>(q, red) / (float)H;
     const float rstd = 1.0f / sqrtf(var + a.f0);
 #pragma unroll
     for (int j = 0; j < NV; ++j) {
-        const int64_t c = 4 * (t + (int64_t)j * TPR);
-        if (live && c < H) {
-            const float4 gm = *reinterpret_cast<const float4*>(a.p0 + c);
-            const float4 bt = *reinterpret_cast<const float4*>(a.p1 + c);
-            float y[4];
-            y[0] = (v[j][0] - mean) * rstd * gm.x + bt.x;
-            y[1] = (v[j][1] - mean) * rstd * gm.y + bt.y;
-            y[2] = (v[j][2] - mean) * rstd * gm.z + bt.z;
-            y[3] = (v[j][3] - mean) * rstd * gm.w + bt.w;
-            uint16_t hi[4];
+        const int c = W * (t + j * TPR);
+        if (!live || c >= H) continue;
+        float gm[W], bt[W];
+        load_run<true>(a.p0, c, gm);
+        load_run<true>(a.p1, c, bt);
 #pragma unroll
-            for (int e = 0; e < 4; ++e) hi[e] = f32_to_bf16_bits(y[e]);
-            if constexpr (OUT32) {
-                *reinterpret_cast<float4*>(reinterpret_cast<float*>(a.y) + off + c) = make_float4(y[0], y[1], y[2], y[3]);
-                if (a.y2) {
-                    uint16_t* y2 = reinterpret_cast<uint16_t*>(a.y2);
-                    *reinterpret_cast<uint2*>(y2 + off + c) = make_uint2(hi[0] | ((uint32_t)hi[1] << 16), hi[2] | ((uint32_t)hi[3] << 16));
-                    if (a.flags & LITHOS_F_OUT_SPLIT) {
-                        uint16_t lo[4];
-#pragma unroll
-                        for (int e = 0; e < 4; ++e) lo[e] = f32_to_bf16_bits(y[e] - bf16_bits_to_f32(hi[e]));
-                        *reinterpret_cast<uint2*>(y2 + a.rows * H + off + c) = make_uint2(lo[0] | ((uint32_t)lo[1] << 16), lo[2] | ((uint32_t)lo[3] << 16));
-                    }
-                }
-            } else {
-                *reinterpret_cast<uint2*>(reinterpret_cast<uint16_t*>(a.y) + off + c) = make_uint2(hi[0] | ((uint32_t)hi[1] << 16), hi[2] | ((uint32_t)hi[3] << 16));
+        for (int e = 0; e < W; ++e) v[j][e] = (v[j][e] - mean) * rstd * gm[e] + bt[e];
+        store_run<OUT32>(a.y, off + c, v[j]);
+        if (OUT32 && a.y2) {
+            store_run<false>(a.y2, off + c, v[j]);
+            if (a.flags & LITHOS_F_OUT_SPLIT) {
+                drop_rounded(v[j]);
+                store_run<false>(a.y2, a.rows * H + off + c, v[j]);
             }
         }
     }
@@ -371,6 +416,56 @@ __global__ __launch_bounds__(256) void rmsnorm_vec_kernel(RowArgs a, AtomArgs at
 }
 
 // ---- softmax(scale * s) -----------------------------------------------------
+// Register-resident rows (n <= 16 * TPR), as in layernorm_vec_kernel: one read of the row and one exponential
+// per element, where the general kernel below reads the row three times and takes the exponential twice
+// (16384 x 1024 bf16: 52 us).
+template <bool IN32, bool OUT32, int TPR, int W>
+__global__ __launch_bounds__(256) void softmax_vec_kernel(RowArgs a, AtomArgs atom)
+{
+    __shared__ float red[4];
+    constexpr int NV = 16 / W;
+    const uint32_t L = atom_logical_block(atom);
+    constexpr int RPB = 256 / TPR;
+    const int64_t row = (int64_t)L * RPB + threadIdx.x / TPR;
+    const int t = threadIdx.x % TPR;
+    const bool live = row < a.rows;
+    const int n = (int)a.cols;
+    const int64_t off = row * n;
+    float v[NV][W];
+    float mx = -INFINITY;
+#pragma unroll
+    for (int j = 0; j < NV; ++j) {
+        const int c = W * (t + j * TPR);
+#pragma unroll
+        for (int e = 0; e < W; ++e) v[j][e] = 0.0f;
+        if (live && c < n) load_run<IN32>(a.x, off + c, v[j]);
+    }
+#pragma unroll
+    for (int j = 0; j < NV; ++j)
+#pragma unroll
+        for (int e = 0; e < W; ++e) {
+            v[j][e] = live && W * (t + j * TPR) < n ? v[j][e] * a.f0 : -INFINITY;
+            mx = fmaxf(mx, v[j][e]);
+        }
+    mx = row_max<TPR>(mx, red);
+    float s = 0.0f;
+#pragma unroll
+    for (int j = 0; j < NV; ++j)
+        if (live && W * (t + j * TPR) < n)
+#pragma unroll
+            for (int e = 0; e < W; ++e) { v[j][e] = expf(v[j][e] - mx); s += v[j][e]; }
+    const float den = row_sum<TPR>(s, red);
+#pragma unroll
+    for (int j = 0; j < NV; ++j) {
+        const int c = W * (t + j * TPR);
+        if (!live || c >= n) continue;
+#pragma unroll
+        for (int e = 0; e < W; ++e) v[j][e] /= den;
+        store_run<OUT32>(a.y, off + c, v[j]);
+    }
+}
+
+// rows longer than 16 * TPR
 template <bool IN32, bool OUT32, int TPR>
 __global__ __launch_bounds__(256) void softmax_kernel(RowArgs a, AtomArgs atom)
 {
@@ -461,33 +556,56 @@ static RowArgs make_args(const lithos_op_t& op)
 
 static int tpr_for(int64_t cols) { return cols <= 1024 ? 64 : 256; }
 
+// Variants of the row kernels: rows of any length read several times; register-resident rows (at most
+// 16 * TPR elements) with runs of 1, or of 4 (fp32) / 8 (bf16 in and out) consecutive elements per access.
+enum { RV_ANY = 0, RV_VEC4 = 1, RV_WIDE = 2, RV_SCALAR = 3 };
+
+// Longest row of the register-resident kernels: 16 elements per thread of 64 or 256 threads per row.
+static int row_variant(const lithos_op_t& op, bool aligned)
+{
+    const int64_t cols = op.dim[1];
+    if (cols > 16 * tpr_for(cols)) return RV_ANY;
+    if (!aligned || cols % 4) return RV_SCALAR;
+    return cols % 8 == 0 && !(op.flags & (LITHOS_F_IN_F32 | LITHOS_F_OUT_F32)) ? RV_WIDE : RV_VEC4;
+}
+
 // The kernel that serves a descriptor (everything but SPIN, whose kernel has its own signature).
 typedef void (*row_fn)(RowArgs, AtomArgs);
 #define PICK2(K) (in32 ? (out32 ? (row_fn)K<true, true> : (row_fn)K<true, false>) : (out32 ? (row_fn)K<false, true> : (row_fn)K<false, false>))
+#define PICK2W(K, W) (in32 ? (out32 ? (row_fn)K<true, true, W> : (row_fn)K<true, false, W>) : (out32 ? (row_fn)K<false, true, W> : (row_fn)K<false, false, W>))
 #define PICK3(K, T) (in32 ? (out32 ? (row_fn)K<true, true, T> : (row_fn)K<true, false, T>) : (out32 ? (row_fn)K<false, true, T> : (row_fn)K<false, false, T>))
+#define PICK3W(K, T, W) (in32 ? (out32 ? (row_fn)K<true, true, T, W> : (row_fn)K<true, false, T, W>) : (out32 ? (row_fn)K<false, true, T, W> : (row_fn)K<false, false, T, W>))
+#define PICKROW(K)                                                                                                    \
+    (variant == RV_WIDE ? (wide ? (row_fn)K<false, false, 256, 8> : (row_fn)K<false, false, 64, 8>)                   \
+                        : variant == RV_VEC4 ? (wide ? PICK3W(K, 256, 4) : PICK3W(K, 64, 4)) : (wide ? PICK3W(K, 256, 1) : PICK3W(K, 64, 1)))
 static row_fn row_kernel(const lithos_op_t& op, int variant)
 {
     const bool in32 = op.flags & LITHOS_F_IN_F32, out32 = op.flags & LITHOS_F_OUT_F32;
     const bool wide = tpr_for(op.dim[1]) == 256;
     switch (op.kind) {
-    case LITHOS_OP_BIAS_ACT: return PICK2(bias_act_kernel);
+    case LITHOS_OP_BIAS_ACT: return variant == RV_WIDE ? PICK2W(bias_act_kernel, 8) : PICK2W(bias_act_kernel, 1);
     case LITHOS_OP_SILU_MUL: return PICK2(silu_mul_kernel);
     case LITHOS_OP_SUM_SLICES:
         return variant == 1 ? (out32 ? (row_fn)sum_slices_kernel<true, true> : (row_fn)sum_slices_kernel<false, true>)
                             : (out32 ? (row_fn)sum_slices_kernel<true, false> : (row_fn)sum_slices_kernel<false, false>);
     case LITHOS_OP_LAYERNORM:
-        if (variant == 1) return wide ? PICK3(layernorm_vec_kernel, 256) : PICK3(layernorm_vec_kernel, 64);   // register-resident rows
+        if (variant) return PICKROW(layernorm_vec_kernel);
         return wide ? PICK3(layernorm_kernel, 256) : PICK3(layernorm_kernel, 64);
     case LITHOS_OP_RMSNORM:
         if (variant == 1) return wide ? PICK3(rmsnorm_vec_kernel, 256) : PICK3(rmsnorm_vec_kernel, 64);
         return wide ? PICK3(rmsnorm_kernel, 256) : PICK3(rmsnorm_kernel, 64);
-    case LITHOS_OP_SOFTMAX: return wide ? PICK3(softmax_kernel, 256) : PICK3(softmax_kernel, 64);
+    case LITHOS_OP_SOFTMAX:
+        if (variant) return PICKROW(softmax_vec_kernel);
+        return wide ? PICK3(softmax_kernel, 256) : PICK3(softmax_kernel, 64);
     case LITHOS_OP_ROPE_KV: return in32 ? (row_fn)rope_kv_kernel<true> : (row_fn)rope_kv_kernel<false>;
     default: return nullptr;
     }
 }
 #undef PICK2
+#undef PICK2W
 #undef PICK3
+#undef PICK3W
+#undef PICKROW
 
 int rowops_plan(const lithos_op_t& op, OpPlan* plan)
 {
@@ -504,6 +622,7 @@ int rowops_plan(const lithos_op_t& op, OpPlan* plan)
         if (!op.out[0]) return fail(LITHOS_EINVAL, "bias_act: null output");
         if ((op.flags & LITHOS_F_BIAS) && !op.in[1]) return fail(LITHOS_EINVAL, "bias_act: BIAS set but in[1] is null");
         blocks = ((uint64_t)rows * cols + 2047) / 2048;
+        plan->variant = cols % 8 == 0 && aligned16(op.in[0]) && aligned16(op.out[0]) && (!op.in[1] || aligned16(op.in[1])) ? RV_WIDE : RV_SCALAR;
         break;
     case LITHOS_OP_SILU_MUL:
         if (!op.out[0]) return fail(LITHOS_EINVAL, "silu_mul: null output");
@@ -528,9 +647,8 @@ int rowops_plan(const lithos_op_t& op, OpPlan* plan)
         if (!op.in[1] || !op.in[2] || !op.out[0]) return fail(LITHOS_EINVAL, "layernorm: null gamma, beta or output");
         if (!(op.flags & LITHOS_F_OUT_F32) && op.out[1]) return fail(LITHOS_EINVAL, "layernorm: a bf16 copy needs OUT_F32");
         blocks = (rows + (256 / tpr_for(cols)) - 1) / (256 / tpr_for(cols));
-        if (cols % 4 == 0 && cols <= 16 * tpr_for(cols) && aligned16(op.in[0]) && aligned16(op.in[1]) && aligned16(op.in[2]) &&
-            aligned16(op.out[0]) && (!op.out[1] || aligned16(op.out[1])))
-            plan->variant = 1;
+        plan->variant = row_variant(op, aligned16(op.in[0]) && aligned16(op.in[1]) && aligned16(op.in[2]) && aligned16(op.out[0]) &&
+                                            (!op.out[1] || aligned16(op.out[1])));
         break;
     case LITHOS_OP_RMSNORM:
         if (!op.in[1] || !op.out[0]) return fail(LITHOS_EINVAL, "rmsnorm: null weight or output");
@@ -541,6 +659,7 @@ int rowops_plan(const lithos_op_t& op, OpPlan* plan)
     case LITHOS_OP_SOFTMAX:
         if (!op.out[0]) return fail(LITHOS_EINVAL, "softmax: null output");
         blocks = (rows + (256 / tpr_for(cols)) - 1) / (256 / tpr_for(cols));
+        plan->variant = row_variant(op, aligned16(op.in[0]) && aligned16(op.out[0]));
         break;
     case LITHOS_OP_ROPE_KV: {
         // dim = rows, n_q, n_kv, d, pos, cap

@@ -180,3 +180,48 @@ def test_row_ops_refuse_bad_arguments():
         with pytest.raises(B.LithosError) as e:
             B.lithos_launch_atomized(ctx(), op)
         assert e.value.code == B.EINVAL
+
+
+@pytest.mark.parametrize("rows,cols", [(1, 1), (5, 3), (9, 8), (6, 12), (3, 63), (130, 64), (4, 1023), (5, 1024), (3, 1025), (2, 1032),
+                                       (3, 4095), (2, 4096), (2, 4097), (2, 4104)])
+@pytest.mark.parametrize("in32,out32", [(False, False), (True, True), (True, False)])
+def test_row_kernels_at_the_edges_of_their_variants(rows, cols, in32, out32):
+    """Rows of one element up to and beyond the longest register-resident row, for every access width (cols a multiple
+    of 8, of 4, odd) and for outputs that are only 4-byte aligned, cut in atoms of 2 blocks."""
+    x32 = inputs.normal_f32((rows, cols), [31, rows, cols], 2.0, 0.5)
+    if not in32:
+        x32 = O.bf16_to_f64(inputs.to_bf16_bits(x32)).astype(np.float32)
+    g, b = inputs.normal_f32((cols,), 32, 0.02, 1.0), inputs.normal_f32((cols,), 33, 0.02)
+    x = torch.from_numpy(x32).cuda() if in32 else torch.from_numpy(x32).cuda().to(torch.bfloat16)
+    gd, bd, dt = torch.from_numpy(g).cuda(), torch.from_numpy(b).cuda(), torch.float32 if out32 else torch.bfloat16
+    x64, g64, b64 = x32.astype(np.float64), g.astype(np.float64), b.astype(np.float64)
+    for shift in (0, 2):                       # elements: the second output buffer is not 16-byte aligned
+        ys = [nan_like((rows * cols + 8,), dt)[shift:shift + rows * cols].view(rows, cols) for _ in range(3)]
+        launch(B.bias_act_op(x, ys[0], rows, cols, gd, gelu=True), atom_blocks=2)
+        launch(B.layernorm_op(x, gd, bd, ys[1], rows, cols, 1e-5), atom_blocks=2)
+        launch(B.softmax_op(x, ys[2], rows, cols, scale=0.7), atom_blocks=2)
+        refs = [O.bias_act(x64, g64, gelu=True), O.layernorm(x64, g64, b64, 1e-5), O.softmax(x64 * 0.7)]
+        # fp32 arithmetic: a few roundings of values up to max |ref| (LayerNorm: of values scaled by 1/std, which
+        # rows of one or three elements make as large as 1/sqrt(eps)); bf16: one step around the rounded value
+        for y, ref, tol in zip(ys, refs, (2e-6, 5e-5, 2e-6)):
+            if out32:
+                f32_close(y, ref, tol * max(1.0, np.abs(ref).max()))
+            else:
+                bf16_close(y, ref, abs_tol=tol, exact_frac=0.98 if rows * cols > 500 else 0.9)
+
+
+def test_gelu_over_its_whole_range():
+    """Both halves of GELU against float64, and the limits.  Error of the lower half, relative: with e = 2^-24, the
+    scaled error function q = 1 - sP carries about 4e absolute (reciprocal 2e, product, last step), that is
+    4e / q with 1/q <= 1 + 1.78 |u| / sqrt 2; the exponent u^2/2 carries 2.5e relative (u*u, constant, sum), so
+    the exponential 2.5e u^2/2 plus 2e of its own; three more products.  Upper half: u (1 - h), at most 4e / 2
+    + 3e."""
+    u = np.concatenate([np.linspace(-13, 13, 20000), [-60.0, -40.0, 40.0, 60.0, 3e4, 0.0]]).astype(np.float32)
+    y = nan_like((1, u.size), torch.float32)
+    launch(B.bias_act_op(torch.from_numpy(u).cuda(), y, 1, u.size, None, gelu=True))
+    from scipy.special import erfc
+    u64, e = u.astype(np.float64), 2.0 ** -24
+    ref = u64 * 0.5 * erfc(-u64 / math.sqrt(2.0))
+    d = np.abs(y.cpu().numpy()[0].astype(np.float64) - ref)
+    lower = e * (5 + 4 * (1 + 1.26 * np.abs(u64)) + 1.25 * u64 ** 2)
+    assert np.all(d <= np.abs(ref) * np.where(u < 0, lower, 5 * e) + 1e-37), np.max(d / np.maximum(np.abs(ref), 1e-37) / e)
