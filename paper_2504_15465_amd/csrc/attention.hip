@@ -37,16 +37,6 @@ struct AttnArgs {
     float* ws;              // dec with splits > 1: partial softmaxes
 };
 
-__device__ __forceinline__ uint16_t attn_f32_to_bf16(float f)
-{
-    uint32_t u = __float_as_uint(f);
-    if ((u & 0x7fffffffu) > 0x7f800000u) return (uint16_t)((u >> 16) | 0x40u);
-    u += 0x7fffu + ((u >> 16) & 1u);
-    return (uint16_t)(u >> 16);
-}
-
-__device__ __forceinline__ float attn_bf16_to_f32(uint16_t h) { return __uint_as_float((uint32_t)h << 16); }
-
 // ---- encoder -------------------------------------------------------------------
 // NKB = seq / 32 key blocks, D = 64.  4 wavefronts when seq >= 128, else seq/32.
 template <int NKB>
@@ -125,11 +115,7 @@ __global__ __launch_bounds__(256) void attn_enc_kernel(AttnArgs a, AtomArgs atom
             for (int gp = 0; gp < 2; ++gp) {
                 uint32_t pw[4];
 #pragma unroll
-                for (int p = 0; p < 4; ++p) {
-                    uint32_t lo = attn_f32_to_bf16(s[kb][8 * gp + 2 * p] * inv);
-                    uint32_t hi = attn_f32_to_bf16(s[kb][8 * gp + 2 * p + 1] * inv);
-                    pw[p] = lo | (hi << 16);
-                }
+                for (int p = 0; p < 4; ++p) pw[p] = pack_bf16(s[kb][8 * gp + 2 * p] * inv, s[kb][8 * gp + 2 * p + 1] * inv);
                 bf16x8 pf = __builtin_bit_cast(bf16x8, make_uint4(pw[0], pw[1], pw[2], pw[3]));
                 const int key0 = kb * 32 + gp * 16 + half * 4;
 #pragma unroll
@@ -147,17 +133,14 @@ __global__ __launch_bounds__(256) void attn_enc_kernel(AttnArgs a, AtomArgs atom
         for (int db = 0; db < D / 32; ++db)
 #pragma unroll
             for (int g = 0; g < 4; ++g) {
-                uint16_t hi[4], lo[4];
+                float v[4] = {o[db][4 * g], o[db][4 * g + 1], o[db][4 * g + 2], o[db][4 * g + 3]};
+                *reinterpret_cast<uint2*>(op + db * 32 + 8 * g + 4 * half) = make_uint2(pack_bf16(v[0], v[1]), pack_bf16(v[2], v[3]));
+                if (a.flags & LITHOS_F_OUT_SPLIT) {
 #pragma unroll
-                for (int e = 0; e < 4; ++e) {
-                    hi[e] = attn_f32_to_bf16(o[db][4 * g + e]);
-                    lo[e] = attn_f32_to_bf16(o[db][4 * g + e] - attn_bf16_to_f32(hi[e]));
-                }
-                *reinterpret_cast<uint2*>(op + db * 32 + 8 * g + 4 * half) =
-                    make_uint2(hi[0] | ((uint32_t)hi[1] << 16), hi[2] | ((uint32_t)hi[3] << 16));
-                if (a.flags & LITHOS_F_OUT_SPLIT)
+                    for (int e = 0; e < 4; ++e) v[e] -= bf16_to_f32(f32_to_bf16(v[e]));
                     *reinterpret_cast<uint2*>(op + (int64_t)a.batch * SEQ * a.n_q * D + db * 32 + 8 * g + 4 * half) =
-                        make_uint2(lo[0] | ((uint32_t)lo[1] << 16), lo[2] | ((uint32_t)lo[3] << 16));
+                        make_uint2(pack_bf16(v[0], v[1]), pack_bf16(v[2], v[3]));
+                }
             }
     }
 }
@@ -237,7 +220,7 @@ __global__ __launch_bounds__(256, 3) void attn_dec_kernel(AttnArgs a, AtomArgs a
         if (h < G) {
             const int64_t idx = (int64_t)b * a.ldq + (g * G + h) * D + d;
             if constexpr (Q32) x = reinterpret_cast<const float*>(a.q)[idx];
-            else x = attn_bf16_to_f32(reinterpret_cast<const uint16_t*>(a.q)[idx]);
+            else x = bf16_to_f32(reinterpret_cast<const uint16_t*>(a.q)[idx]);
             x *= a.scale;
         }
         const uint32_t hi = __float_as_uint(x) & 0xffff0000u;
@@ -372,7 +355,7 @@ __global__ __launch_bounds__(256, 3) void attn_dec_kernel(AttnArgs a, AtomArgs a
             const float r = num / den;
             const int64_t idx = (int64_t)b * ((int64_t)a.n_q * D) + (g * G + h) * D + d;
             if constexpr (O32) reinterpret_cast<float*>(a.o)[idx] = r;
-            else reinterpret_cast<uint16_t*>(a.o)[idx] = attn_f32_to_bf16(r);
+            else reinterpret_cast<uint16_t*>(a.o)[idx] = f32_to_bf16(r);
         } else {
             float* ws = a.ws;
             const int64_t row = ((int64_t)bg * S + sp) * G + h;
@@ -430,7 +413,7 @@ __global__ __launch_bounds__(256) void attn_merge_kernel(AttnArgs a, AtomArgs at
         const float r = num / den;
         const int64_t idx = (int64_t)b * ((int64_t)a.n_q * D) + (g * G + h) * D + d;
         if constexpr (O32) reinterpret_cast<float*>(a.o)[idx] = r;
-        else reinterpret_cast<uint16_t*>(a.o)[idx] = attn_f32_to_bf16(r);
+        else reinterpret_cast<uint16_t*>(a.o)[idx] = f32_to_bf16(r);
     }
 }
 

@@ -24,8 +24,6 @@
 namespace lithos {
 
 typedef __bf16 pf_bf16x8 __attribute__((ext_vector_type(8)));
-typedef __bf16 pf_bf16x2 __attribute__((ext_vector_type(2)));
-typedef float pf_f32x2 __attribute__((ext_vector_type(2)));
 typedef float pf_f32x16 __attribute__((ext_vector_type(16)));
 typedef short pf_s16x4 __attribute__((ext_vector_type(4)));
 
@@ -47,12 +45,6 @@ __device__ __forceinline__ int pf_k_index(int key, int chunk) { return key * PF_
 // V block [64 keys][128 d]: chunk c of key k at chunk c ^ ((k & 3) << 2), so the four keys that one
 // transposing load touches fall into different banks.
 __device__ __forceinline__ int pf_v_index(int key, int d) { return key * PF_D + ((((d >> 3) ^ ((key & 3) << 2))) << 3) + (d & 7); }
-
-__device__ __forceinline__ uint32_t pf_pack_bf16(float lo, float hi)
-{
-    pf_f32x2 f = {lo, hi};
-    return __builtin_bit_cast(uint32_t, __builtin_convertvector(f, pf_bf16x2));   // round to nearest even
-}
 
 // One block of keys and values is 1024 chunks of 16 bytes per operand, four per thread, held in
 // eight named registers between the fetch and the store to LDS one iteration later (an array
@@ -197,7 +189,7 @@ __global__ __launch_bounds__(256, 2) void attn_prefill_kernel(PrefillArgs a, Ato
             for (int gp = 0; gp < 2; ++gp) {
                 uint32_t pw[4];
 #pragma unroll
-                for (int p = 0; p < 4; ++p) pw[p] = pf_pack_bf16(s[sub][8 * gp + 2 * p], s[sub][8 * gp + 2 * p + 1]);
+                for (int p = 0; p < 4; ++p) pw[p] = pack_bf16(s[sub][8 * gp + 2 * p], s[sub][8 * gp + 2 * p + 1]);
                 const pf_bf16x8 pf = __builtin_bit_cast(pf_bf16x8, make_uint4(pw[0], pw[1], pw[2], pw[3]));
                 // source lane sl of a 16-lane group supplies key krow, d-rows 4 (sl%4) .. +3 of the group's 16
                 const int krow = sub * 32 + gp * 16 + 4 * (grp >> 1) + (sl >> 2);
@@ -222,8 +214,8 @@ __global__ __launch_bounds__(256, 2) void attn_prefill_kernel(PrefillArgs a, Ato
 #pragma unroll
         for (int q4 = 0; q4 < 4; ++q4)
             *reinterpret_cast<uint2*>(op + db * 32 + 8 * q4 + 4 * half) =
-                make_uint2(pf_pack_bf16(o[db][4 * q4] * inv, o[db][4 * q4 + 1] * inv),
-                           pf_pack_bf16(o[db][4 * q4 + 2] * inv, o[db][4 * q4 + 3] * inv));
+                make_uint2(pack_bf16(o[db][4 * q4] * inv, o[db][4 * q4 + 1] * inv),
+                           pack_bf16(o[db][4 * q4 + 2] * inv, o[db][4 * q4 + 3] * inv));
   }
 }
 

@@ -67,6 +67,21 @@ inline hipError_t launch_kernel(void (*k)(Params...), dim3 grid, dim3 block, hip
 // once per (device, kernel, size) and remembered; `fallback` if the runtime cannot say.
 uint32_t cached_occupancy(const void* kernel, int threads, uint32_t fallback);
 
+// fp32 -> bf16 bits, round to nearest even: one conversion instruction for two values (the integer form of
+// the rounding took six for each, which bound the row kernels and the epilogues of short GEMMs).
+typedef __bf16 lithos_bf16x2 __attribute__((ext_vector_type(2)));
+typedef float lithos_f32x2 __attribute__((ext_vector_type(2)));
+
+__device__ __forceinline__ uint32_t pack_bf16(float lo, float hi)
+{
+    const lithos_f32x2 f = {lo, hi};
+    return __builtin_bit_cast(uint32_t, __builtin_convertvector(f, lithos_bf16x2));
+}
+
+__device__ __forceinline__ uint16_t f32_to_bf16(float f) { return (uint16_t)pack_bf16(f, f); }
+
+__device__ __forceinline__ float bf16_to_f32(uint16_t h) { return __uint_as_float((uint32_t)h << 16); }
+
 // GELU u * Phi(u), Phi(u) = erfc(-u / sqrt 2) / 2, by one formula for every u: with x = |u| / sqrt 2,
 // erfc(x) exp(x^2) = 1 - s P(s), s = p x / (1 + p x), P of degree 8 fitted (iteratively reweighted least
 // squares, float64) to 8e-9 relative; the lower half of Phi then keeps its RELATIVE accuracy where

@@ -39,14 +39,6 @@ __device__ __forceinline__ void slice_ktiles(const GemmArgs& g, uint32_t z, int 
     kt1 = (int)(((int64_t)(z + 1) * KT) / g.k_slices);
 }
 
-__device__ __forceinline__ uint16_t f32_to_bf16_rne(float f)
-{
-    uint32_t u = __float_as_uint(f);
-    if ((u & 0x7fffffffu) > 0x7f800000u) return (uint16_t)((u >> 16) | 0x40u);  // quiet NaN
-    u += 0x7fffu + ((u >> 16) & 1u);
-    return (uint16_t)(u >> 16);
-}
-
 // Compile-time loop: the body sees its index as a constant, so register
 // arrays indexed with it never become memory.
 template <typename F, int... Is>
@@ -69,11 +61,11 @@ __device__ __forceinline__ void epilogue_store(const GemmArgs& g, int m, int n, 
     if (g.flags & LITHOS_F_OUT_F32) {
         reinterpret_cast<float*>(g.C)[(int64_t)m * g.ldc + n] = v;
     } else {
-        uint16_t hi = f32_to_bf16_rne(v);
+        uint16_t hi = f32_to_bf16(v);
         reinterpret_cast<uint16_t*>(g.C)[(int64_t)m * g.ldc + n] = hi;
         if (g.flags & LITHOS_F_OUT_SPLIT)       // second bf16 carries what the first one dropped
             reinterpret_cast<uint16_t*>(g.C)[g.c_plane + (int64_t)m * g.ldc + n] =
-                f32_to_bf16_rne(v - __uint_as_float((uint32_t)hi << 16));
+                f32_to_bf16(v - __uint_as_float((uint32_t)hi << 16));
     }
 }
 
@@ -83,7 +75,7 @@ __device__ __forceinline__ uint16_t epilogue_bf16(const GemmArgs& g, int m, int 
     if (g.flags & LITHOS_F_BIAS) v += g.bias[n];
     if (g.flags & LITHOS_F_GELU) v = gelu_erf(v);
     if (g.flags & LITHOS_F_RESIDUAL) v += g.resid[(int64_t)m * g.ldr + n];
-    return f32_to_bf16_rne(v);
+    return f32_to_bf16(v);
 }
 
 // ---- epilogue of a full bf16 tile through LDS ---------------------------------
@@ -131,15 +123,13 @@ __device__ __forceinline__ void stage_block_values(uint16_t* st, int r, int n_ti
     static_for<4>([&](auto qq) {
         constexpr int q = decltype(qq)::value;
         const int nl = n_tile + 8 * q + 4 * (lane >> 5);
-        uint16_t h[4];
+        float v[4];
 #pragma unroll
         for (int t = 0; t < 4; ++t) {
-            const float v = acc[4 * q + t];
-            h[t] = f32_to_bf16_rne(v);
-            if constexpr (LO) h[t] = f32_to_bf16_rne(v - __uint_as_float((uint32_t)h[t] << 16));
+            v[t] = acc[4 * q + t];
+            if constexpr (LO) v[t] -= bf16_to_f32(f32_to_bf16(v[t]));
         }
-        *reinterpret_cast<uint2*>(st + stage_index<BN>(r, nl >> 3) + (nl & 4)) =
-            make_uint2(h[0] | ((uint32_t)h[1] << 16), h[2] | ((uint32_t)h[3] << 16));
+        *reinterpret_cast<uint2*>(st + stage_index<BN>(r, nl >> 3) + (nl & 4)) = make_uint2(pack_bf16(v[0], v[1]), pack_bf16(v[2], v[3]));
     });
 }
 

@@ -23,28 +23,18 @@ struct RowArgs {
     int64_t aux[5];
 };
 
-__device__ __forceinline__ float bf16_bits_to_f32(uint16_t h) { return __uint_as_float((uint32_t)h << 16); }
-
-__device__ __forceinline__ uint16_t f32_to_bf16_bits(float f)
-{
-    uint32_t u = __float_as_uint(f);
-    if ((u & 0x7fffffffu) > 0x7f800000u) return (uint16_t)((u >> 16) | 0x40u);
-    u += 0x7fffu + ((u >> 16) & 1u);
-    return (uint16_t)(u >> 16);
-}
-
 template <bool F32>
 __device__ __forceinline__ float load_elem(const void* p, int64_t i)
 {
     if constexpr (F32) return reinterpret_cast<const float*>(p)[i];
-    else return bf16_bits_to_f32(reinterpret_cast<const uint16_t*>(p)[i]);
+    else return bf16_to_f32(reinterpret_cast<const uint16_t*>(p)[i]);
 }
 
 template <bool F32>
 __device__ __forceinline__ void store_elem(void* p, int64_t i, float v)
 {
     if constexpr (F32) reinterpret_cast<float*>(p)[i] = v;
-    else reinterpret_cast<uint16_t*>(p)[i] = f32_to_bf16_bits(v);
+    else reinterpret_cast<uint16_t*>(p)[i] = f32_to_bf16(v);
 }
 
 __device__ __forceinline__ float wave_sum(float v)
@@ -123,7 +113,7 @@ __device__ __forceinline__ void store_run(void* p, int64_t i, const float (&v)[W
     } else {
         uint32_t u[W / 2];
 #pragma unroll
-        for (int q = 0; q < W / 2; ++q) u[q] = f32_to_bf16_bits(v[2 * q]) | ((uint32_t)f32_to_bf16_bits(v[2 * q + 1]) << 16);
+        for (int q = 0; q < W / 2; ++q) u[q] = pack_bf16(v[2 * q], v[2 * q + 1]);
         uint16_t* h = reinterpret_cast<uint16_t*>(p) + i;
         if constexpr (W == 8) *reinterpret_cast<uint4*>(h) = make_uint4(u[0], u[1], u[2], u[3]);
         else *reinterpret_cast<uint2*>(h) = make_uint2(u[0], u[1]);
@@ -135,7 +125,7 @@ template <int W>
 __device__ __forceinline__ void drop_rounded(float (&v)[W])
 {
 #pragma unroll
-    for (int e = 0; e < W; ++e) v[e] -= bf16_bits_to_f32(f32_to_bf16_bits(v[e]));
+    for (int e = 0; e < W; ++e) v[e] -= bf16_to_f32(f32_to_bf16(v[e]));
 }
 
 // ---- y = act(x + bias): 2048 consecutive elements per block ---------------
@@ -222,8 +212,7 @@ __global__ __launch_bounds__(256) void sum_slices_kernel(RowArgs a, AtomArgs ato
             *reinterpret_cast<float4*>(reinterpret_cast<float*>(a.y) + r * ldy + c) = make_float4(v[0], v[1], v[2], v[3]);
         } else if constexpr (VEC) {
             *reinterpret_cast<uint2*>(reinterpret_cast<uint16_t*>(a.y) + r * ldy + c) =
-                make_uint2(f32_to_bf16_bits(v[0]) | ((uint32_t)f32_to_bf16_bits(v[1]) << 16),
-                           f32_to_bf16_bits(v[2]) | ((uint32_t)f32_to_bf16_bits(v[3]) << 16));
+                make_uint2(pack_bf16(v[0], v[1]), pack_bf16(v[2], v[3]));
         } else {
             store_elem<OUT32>(a.y, r * ldy + c, v[0]);
         }
@@ -272,10 +261,10 @@ __global__ __launch_bounds__(256) void layernorm_kernel(RowArgs a, AtomArgs atom
         float v = (load_elem<IN32>(a.x, off + c) - mean) * rstd * a.p0[c] + a.p1[c];
         store_elem<OUT32>(a.y, off + c, v);
         if (OUT32 && a.y2) {
-            uint16_t hi = f32_to_bf16_bits(v);
+            uint16_t hi = f32_to_bf16(v);
             reinterpret_cast<uint16_t*>(a.y2)[off + c] = hi;
             if (a.flags & LITHOS_F_OUT_SPLIT)
-                reinterpret_cast<uint16_t*>(a.y2)[a.rows * H + off + c] = f32_to_bf16_bits(v - bf16_bits_to_f32(hi));
+                reinterpret_cast<uint16_t*>(a.y2)[a.rows * H + off + c] = f32_to_bf16(v - bf16_to_f32(hi));
         }
     }
 }
@@ -405,11 +394,7 @@ __global__ __launch_bounds__(256) void rmsnorm_vec_kernel(RowArgs a, AtomArgs at
             if constexpr (OUT32) {
                 *reinterpret_cast<float4*>(reinterpret_cast<float*>(a.y) + off + c) = make_float4(y[0], y[1], y[2], y[3]);
             } else {
-                uint16_t h[4];
-#pragma unroll
-                for (int e = 0; e < 4; ++e) h[e] = f32_to_bf16_bits(y[e]);
-                *reinterpret_cast<uint2*>(reinterpret_cast<uint16_t*>(a.y) + off + c) =
-                    make_uint2(h[0] | ((uint32_t)h[1] << 16), h[2] | ((uint32_t)h[3] << 16));
+                *reinterpret_cast<uint2*>(reinterpret_cast<uint16_t*>(a.y) + off + c) = make_uint2(pack_bf16(y[0], y[1]), pack_bf16(y[2], y[3]));
             }
         }
     }
@@ -516,11 +501,11 @@ __global__ __launch_bounds__(256) void rope_kv_kernel(RowArgs a, AtomArgs atom)
             float r0 = x0 * cs - x1 * sn, r1 = x1 * cs + x0 * sn;
             store_elem<F32>(head, hoff + e, r0);
             store_elem<F32>(head, hoff + e + half, r1);
-            if (dst) { dst[e] = f32_to_bf16_bits(r0); dst[e + half] = f32_to_bf16_bits(r1); }
+            if (dst) { dst[e] = f32_to_bf16(r0); dst[e + half] = f32_to_bf16(r1); }
         }
     } else {
         uint16_t* dst = vc + ((row * cap + pos) * n_kv + (slot - n_q - n_kv)) * d;
-        for (int64_t e = lane; e < d; e += 64) dst[e] = f32_to_bf16_bits(load_elem<F32>(head, hoff + e));
+        for (int64_t e = lane; e < d; e += 64) dst[e] = f32_to_bf16(load_elem<F32>(head, hoff + e));
     }
 }
 
