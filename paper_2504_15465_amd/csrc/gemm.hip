@@ -25,7 +25,7 @@ namespace lithos {
 
 // ---- host side -------------------------------------------------------------
 
-static int tile_threads(int variant) { return (variant == 30 || variant == 31) ? 512 : (variant < 10 || variant >= 40) ? SKINNY_WAVES * 64 : 256; }
+static int tile_threads(int variant) { return variant == V_TILE128 ? 256 : 512; }
 
 // full bf16 tiles can leave through LDS when whole 16-byte pieces of C rows are addressable
 // (fp32 tiles of the same kernels are stored from registers, 16 bytes per lane)

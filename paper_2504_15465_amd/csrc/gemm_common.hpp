@@ -9,6 +9,9 @@ namespace lithos {
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
+typedef const __attribute__((address_space(1))) void* gptr_t;
+typedef __attribute__((address_space(3))) void* lptr_t;
+typedef short s16x4 __attribute__((ext_vector_type(4)));
 
 struct GemmArgs {
     const uint16_t* A;
@@ -100,19 +103,29 @@ __device__ __forceinline__ int stage_index(int r, int p)
 // accumulator block with exchanged operands: lane holds output row (lane & 31) of the
 // block and columns 8*q + 4*(lane >> 5) + t, q = 0..3, t = 0..3
 
-// bias, GELU and residual applied in place (a no-op without those flags)
+// four consecutive floats, 4-byte aligned (one 16-byte load; bias and residual need no alignment)
+typedef float f32x4_u __attribute__((ext_vector_type(4), aligned(4)));
+
+// bias, GELU and residual applied in place (a no-op without those flags); a lane's columns 8*q + 4*(lane >> 5) .. +3
+// are one 16-byte load of each operand.  Rows and column quads beyond the matrix (N % 4 == 0 then) compute on
+// its last ones and are not stored.
 __device__ __forceinline__ void epilogue_block_swapped(const GemmArgs& g, int m, int n_glob, f32x16& acc, int lane)
 {
     if (!(g.flags & (LITHOS_F_BIAS | LITHOS_F_GELU | LITHOS_F_RESIDUAL))) return;   // uniform
-    static_for<16>([&](auto ee) {
-        constexpr int e = decltype(ee)::value;
-        const int n = n_glob + 8 * (e >> 2) + 4 * (lane >> 5) + (e & 3);
-        float v = acc[e];
-        if (g.flags & LITHOS_F_BIAS) v += g.bias[n];
-        if (g.flags & LITHOS_F_GELU) v = gelu_erf(v);
-        if (g.flags & LITHOS_F_RESIDUAL) v += g.resid[(int64_t)m * g.ldr + n];
-        acc[e] = v;
-    });
+    const float* const rrow = g.resid + (int64_t)min(m, g.M - 1) * g.ldr;
+    f32x4_u bv[4], rv[4];
+    const auto col = [&](int q) { return min(n_glob + 8 * q + 4 * (lane >> 5), g.N - 4); };
+    if (g.flags & LITHOS_F_BIAS) {
+#pragma unroll
+        for (int q = 0; q < 4; ++q) bv[q] = *reinterpret_cast<const f32x4_u*>(g.bias + col(q));
+    }
+    if (g.flags & LITHOS_F_RESIDUAL) {
+#pragma unroll
+        for (int q = 0; q < 4; ++q) rv[q] = *reinterpret_cast<const f32x4_u*>(rrow + col(q));
+    }
+    if (g.flags & LITHOS_F_BIAS) static_for<16>([&](auto ee) { constexpr int e = decltype(ee)::value; acc[e] += bv[e >> 2][e & 3]; });
+    if (g.flags & LITHOS_F_GELU) static_for<16>([&](auto ee) { constexpr int e = decltype(ee)::value; acc[e] = gelu_erf(acc[e]); });
+    if (g.flags & LITHOS_F_RESIDUAL) static_for<16>([&](auto ee) { constexpr int e = decltype(ee)::value; acc[e] += rv[e >> 2][e & 3]; });
 }
 
 // the block's values rounded to bf16 into the staged tile; LO: what the first rounding dropped,
@@ -142,23 +155,16 @@ __device__ __forceinline__ void stage_block(const GemmArgs& g, uint16_t* st, int
     stage_block_values<BN, false>(st, r, n_tile, v, lane);
 }
 
-// the same block of a full fp32 tile: 16 bytes (four columns) per lane and store
+// the same block of an fp32 tile: 16 bytes (four columns) per lane and store, what lies beyond the matrix left out
 __device__ __forceinline__ void store_block_swapped_f32(const GemmArgs& g, float* C, int m, int n_glob, const f32x16& acc, int lane)
 {
-    const bool plain = !(g.flags & (LITHOS_F_BIAS | LITHOS_F_GELU | LITHOS_F_RESIDUAL));   // uniform
+    f32x16 v = acc;
+    epilogue_block_swapped(g, m, n_glob, v, lane);
     static_for<4>([&](auto qq) {
         constexpr int q = decltype(qq)::value;
         const int n = n_glob + 8 * q + 4 * (lane >> 5);
-        float v[4] = {acc[4 * q], acc[4 * q + 1], acc[4 * q + 2], acc[4 * q + 3]};
-        if (!plain) {
-#pragma unroll
-            for (int t = 0; t < 4; ++t) {
-                if (g.flags & LITHOS_F_BIAS) v[t] += g.bias[n + t];
-                if (g.flags & LITHOS_F_GELU) v[t] = gelu_erf(v[t]);
-                if (g.flags & LITHOS_F_RESIDUAL) v[t] += g.resid[(int64_t)m * g.ldr + n + t];
-            }
-        }
-        *reinterpret_cast<float4*>(C + (int64_t)m * g.ldc + n) = make_float4(v[0], v[1], v[2], v[3]);
+        if (m < g.M && n < g.N)
+            *reinterpret_cast<float4*>(C + (int64_t)m * g.ldc + n) = make_float4(v[4 * q], v[4 * q + 1], v[4 * q + 2], v[4 * q + 3]);
     });
 }
 

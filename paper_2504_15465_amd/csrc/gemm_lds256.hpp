@@ -18,10 +18,6 @@ namespace lithos {
 // k-row s/4, and lane l receives row l of the four k-rows: 4 consecutive k of one row,
 // which is the MFMA operand layout.  Two such loads make a fragment; nothing is
 // transposed in registers.
-typedef const __attribute__((address_space(1))) void* gptr_t;
-typedef __attribute__((address_space(3))) void* lptr_t;
-typedef short s16x4 __attribute__((ext_vector_type(4)));
-typedef short s16x8 __attribute__((ext_vector_type(8)));
 
 // [64 k][256 rows] tile: 16-byte chunk c of k-row k is stored at chunk c ^ ((k & 3) << 2), so
 // the four k-rows that one transposing load touches fall into different banks.

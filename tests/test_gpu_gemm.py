@@ -652,3 +652,33 @@ def test_k_sliced_gemm_keeps_its_slices_under_a_callers_grid():
     B.lithos_partition_sync(ctx(), None)
     assert not torch.isnan(p1).any()
     assert bits_equal(p0, p1)
+
+
+@pytest.mark.parametrize("tile,split", [(64, False), (64, True), (128, False), (128, True)])
+@pytest.mark.parametrize("k", [8, 56, 64, 72, 128, 200, 264])
+def test_pipelined_tiles_at_every_remainder_of_k(tile, split, k):
+    """The tile kernels fetch k-tiles ahead and in two groups: fewer tiles than stages, a group without a tile, a last
+    tile of 8 k; ragged M and N in whole 16-byte pieces (bf16 and fp32 C with a misaligned bias and residual).
+    fp32 sums of K products: at most K * 2^-24 of the sum of magnitudes (K / 4 for uniform operands) from the oracle."""
+    m, n = tile + 8, tile + 24
+    a_bits, b_bits = inputs.gemm_operands(m, n, k, seed=k + tile, tb=False)
+    a = dev_bits(a_bits)
+    ref = O.gemm(a_bits, b_bits)
+    if split:       # lo plane = hi plane scaled by 2^-8: exactly representable
+        a = torch.stack([a, (a.float() * 2.0 ** -8).to(torch.bfloat16)]).contiguous()
+        ref = ref * (1.0 + 2.0 ** -8)
+    pad = torch.randn(n + 1 + m * (n + 1) + 1, device="cuda")
+    bias, resid = pad[1:n + 1], pad[n + 2:].view(m, n + 1)[:, :n]
+    b = dev_bits(b_bits)
+    full = ref + bias.double().cpu().numpy() + resid.double().cpu().numpy()
+    for dt in (torch.float32, torch.bfloat16):
+        c = nan_like((m, n), dt)
+        torch.cuda.synchronize()
+        op = B.gemm_op(a, b, c, m, n, k, tile=tile, a_split=split, bias=bias, residual=resid, ldr=n + 1)
+        B.lithos_launch_atomized(ctx(), op, (0, 0, 0), 2)
+        B.lithos_partition_sync(ctx(), None)
+        bound = 2.0 ** -24 * k * (k / 4 + 1) + 2.0 ** -19
+        if dt is torch.float32:
+            assert np.abs(c.cpu().numpy().astype(np.float64) - full).max() <= bound
+        else:
+            bf16_close(c, full, abs_tol=bound)
