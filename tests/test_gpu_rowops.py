@@ -125,6 +125,27 @@ def test_softmax(rows, n):
     bf16_close(pb, O.softmax(O.bf16_to_f64(bits) * 0.125))
 
 
+@pytest.mark.parametrize("n", [77, 1000, 1024, 2048])
+def test_softmax_of_masked_and_far_apart_scores(n):
+    """Rows with masked scores (-inf and the type's lowest value), with subnormal and vanishing probabilities, and
+    with every score masked (NaN).  The difference to the maximum (60 +- 10) rounds to 2^-18, which is the probability's
+    relative error, on top of 2e-6; or the smallest normal number where the probability is below it."""
+    rng = np.random.default_rng(n)
+    s = rng.normal(0.0, 2.0, (6, n)).astype(np.float32)
+    s[0, ::3] = -np.inf
+    s[1, 1:] = np.finfo(np.float32).min
+    s[2] = np.linspace(0.0, -120.0, n)
+    s[3, n // 2] = 60.0
+    s[4] = -np.inf
+    p = nan_like((6, n), torch.float32)
+    launch(B.softmax_op(torch.from_numpy(s).cuda(), p, 6, n, scale=1.0))
+    got = p.cpu().numpy().astype(np.float64)
+    assert np.isnan(got[4]).all()
+    rows = [0, 1, 2, 3, 5]
+    ref = O.softmax(s[rows].astype(np.float64))
+    assert (np.abs(got[rows] - ref) <= (2e-6 + 2.0 ** -18) * ref + np.finfo(np.float32).tiny).all()
+
+
 @pytest.mark.parametrize("rows,f", [(8, 14336), (3, 1000)])
 def test_silu_mul(rows, f):
     bits = inputs.normal_bits((rows, 2 * f), 9, 2.0)
