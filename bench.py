@@ -96,7 +96,7 @@ def be_gemm_8192(B, inputs, torch, tile):
     a, b = inputs.bits_to_torch(a_bits, "cuda").contiguous(), inputs.bits_to_torch(b_bits, "cuda").contiguous()
     c = torch.empty((n, n), dtype=torch.bfloat16, device="cuda")
     op = B.gemm_op(a, b, c, n, n, n, tile=tile)
-    desc = ("gemm_lds256_kernel" if tile == 256 else "gemm_tile_kernel<%d,%d>" % (tile, tile)) + \
+    desc = ("gemm_lds256_kernel" if tile == 256 else "gemm_lds_kernel<%d,%d>" % (tile, tile)) + \
         " 8192^3 bf16 (A [M,K], B [K,N]), whole launch, 256 CUs"
     return dict(ops=[op], flop=2.0 * n ** 3, dominant=(op, 2.0 * n ** 3, desc), host=(a_bits, b_bits),
                 text="bf16 8192^3 GEMMs back to back")

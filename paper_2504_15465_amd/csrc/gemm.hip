@@ -5,8 +5,9 @@
 //  * gemm_lds256_kernel (gemm_lds256.hpp, gemm_lds256_{wide,elem}.hip) - 256x256 tiles, K % 64 == 0, any operand
 //    layout: global memory straight into LDS, k-strided operands read with the
 //    transposing LDS load; the best-effort and training-shaped GEMMs;
-//  * gemm_tile_kernel (gemm_tile.hpp, gemm_tile{64,128}.hip, gemm_tile256_{wide,elem}.hip) - 64/128/256
-//    tiles through registers, ragged K, split-bf16 A;
+//  * gemm_lds_kernel (gemm_lds.hpp, gemm_tile{64,128}.hip) - 64 and 128 tiles, any K % 8 == 0, split-bf16 A;
+//    global memory straight into LDS, two or three stages;
+//  * gemm_tile_kernel (gemm_tile.hpp, gemm_tile256_{wide,elem}.hip) - 256 tiles with any other K, through registers;
 //  * gemm_skinny_*_kernel (gemm_skinny.hip) - M <= 32 rows (bf16 or fp32
 //    activations) against a [N,K] bf16 weight matrix: HBM-bound, the weights are
 //    streamed exactly once.  The products still go through MFMA 16x16x32

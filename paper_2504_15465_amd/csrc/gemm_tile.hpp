@@ -1,6 +1,6 @@
-// LDS-staged MFMA tile GEMM (v_mfma_f32_32x32x16_bf16) for any operand layout:
-// 64x64, 128x128 or 256x256 output tiles, BK = 64.  Every workgroup computes the
-// tile named by its LOGICAL block index (LithOS Section 4.4).
+// Register-staged MFMA tile GEMM (v_mfma_f32_32x32x16_bf16) for any operand layout: 256x256 output tiles, BK = 64,
+// the K that gemm_lds256_kernel does not take (K % 64 != 0).  Every workgroup computes the tile named by its
+// LOGICAL block index (LithOS Section 4.4).
 #pragma once
 #include "gemm_common.hpp"
 
@@ -92,24 +92,21 @@ struct TileStage {
     }
 };
 
-// SPLIT: A is a pair of bf16 planes (hi, lo) whose sum carries ~16 significant
-// bits of the activation; both planes are multiplied with the same B operand.
 // ST: full bf16 tiles leave through LDS (operands exchanged in the MFMA, see stage_block).
-// Registers are capped so that 256x256 tiles keep two wavefronts per SIMD (one 8-wave workgroup
-// per CU), 128x128 tiles three workgroups and 64x64 tiles four: left alone, the compiler spends
-// the whole register file on hoisted epilogue addresses and halves the occupancy.
-template <int BM, int BN, int WGM, int WGN, bool TA, bool TB, bool SPLIT, bool ST>
-__global__ __launch_bounds__(WGM * WGN * 64, BM >= 256 ? 2 : BM >= 128 ? 3 : 4)
+// Registers are capped so that a 256x256 tile keeps two wavefronts per SIMD (one 8-wave workgroup
+// per CU): left alone, the compiler spends the whole register file on hoisted epilogue addresses and halves the
+// occupancy.
+template <int BM, int BN, int WGM, int WGN, bool TA, bool TB, bool ST>
+__global__ __launch_bounds__(WGM * WGN * 64, 2)
 void gemm_tile_kernel(GemmArgs g, AtomArgs atom)
 {
     constexpr int T = WGM * WGN * 64, BK = 64;
     constexpr int WM = BM / WGM, WN = BN / WGN, MI = WM / 32, NI = WN / 32;
     // operand buffers; a staged epilogue needs room for the whole bf16 output tile
-    constexpr int OPERAND_ELEMS = (BM + BN) * BK + (SPLIT ? BM * BK : 0);
+    constexpr int OPERAND_ELEMS = (BM + BN) * BK;
     __shared__ __attribute__((aligned(16))) uint16_t smem[ST && BM * BN > OPERAND_ELEMS ? BM * BN : OPERAND_ELEMS];
     uint16_t* const As = smem;
     uint16_t* const Bs = smem + BM * BK;
-    uint16_t* const As2 = smem + (BM + BN) * BK;
 
     const uint32_t L = atom_logical_block(atom);
     const Block3 blk = atom_delinearize(L, atom);
@@ -129,7 +126,6 @@ void gemm_tile_kernel(GemmArgs g, AtomArgs atom)
             for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.0f;
 
     TileStage<BM, T, TA> sa;        // A is k-strided in memory when transposed
-    TileStage<SPLIT ? BM : T / 8, T, TA && SPLIT> sa2;   // lo plane of A (a dummy 32-row stage when unused)
     TileStage<BN, T, !TB> sb;       // B is k-strided in memory when NOT transposed
 
     int kt0, kt1;
@@ -138,10 +134,8 @@ void gemm_tile_kernel(GemmArgs g, AtomArgs atom)
     if (g.k_slices > 1) g.C = reinterpret_cast<float*>(g.C) + (int64_t)blk.z * g.c_slice;
     if (kt0 < kt1) {
         sa.load(g.A, g.lda, m0, g.M, kt0 * BK, g.K, tid);
-        if constexpr (SPLIT) sa2.load(g.A + g.a_plane, g.lda, m0, g.M, kt0 * BK, g.K, tid);
         sb.load(g.B, g.ldb, n0, g.N, kt0 * BK, g.K, tid);
         sa.store(As, tid);
-        if constexpr (SPLIT) sa2.store(As2, tid);
         sb.store(Bs, tid);
     }
     __syncthreads();
@@ -149,19 +143,16 @@ void gemm_tile_kernel(GemmArgs g, AtomArgs atom)
     for (int kt = kt0; kt < KT; ++kt) {
         if (kt + 1 < KT) {          // next tile's global loads fly during the MFMAs
             sa.load(g.A, g.lda, m0, g.M, (kt + 1) * BK, g.K, tid);
-            if constexpr (SPLIT) sa2.load(g.A + g.a_plane, g.lda, m0, g.M, (kt + 1) * BK, g.K, tid);
-            sb.load(g.B, g.ldb, n0, g.N, (kt + 1) * BK, g.K, tid);
+                sb.load(g.B, g.ldb, n0, g.N, (kt + 1) * BK, g.K, tid);
         }
 #pragma unroll
         for (int kk = 0; kk < BK / 16; ++kk) {
             const int kc = kk * 2 + (lane >> 5);
-            bf16x8 af[MI], af2[MI], bfr[NI];
+            bf16x8 af[MI], bfr[NI];
 #pragma unroll
             for (int i = 0; i < MI; ++i) {
                 int row = wm * WM + i * 32 + (lane & 31);
                 af[i] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const uint4*>(As + lds_index(row, kc)));
-                if constexpr (SPLIT)
-                    af2[i] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const uint4*>(As2 + lds_index(row, kc)));
             }
 #pragma unroll
             for (int j = 0; j < NI; ++j) {
@@ -172,10 +163,6 @@ void gemm_tile_kernel(GemmArgs g, AtomArgs atom)
             for (int i = 0; i < MI; ++i)
 #pragma unroll
                 for (int j = 0; j < NI; ++j) {
-                    if constexpr (SPLIT && ST)    // small term first
-                        acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(bfr[j], af2[i], acc[i][j], 0, 0, 0);
-                    else if constexpr (SPLIT)
-                        acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(af2[i], bfr[j], acc[i][j], 0, 0, 0);
                     if constexpr (ST)
                         acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(bfr[j], af[i], acc[i][j], 0, 0, 0);
                     else
@@ -185,7 +172,6 @@ void gemm_tile_kernel(GemmArgs g, AtomArgs atom)
         __syncthreads();            // every wave is done reading this tile
         if (kt + 1 < KT) {
             sa.store(As, tid);
-            if constexpr (SPLIT) sa2.store(As2, tid);
             sb.store(Bs, tid);
             __syncthreads();
         }
@@ -249,14 +235,9 @@ void gemm_tile_kernel(GemmArgs g, AtomArgs atom)
 }
 
 #define LITHOS_TILE_PICK4(BMN, WGM, WGN, ST)                                                    \
-    (ta ? (tb ? (gemm_fn)gemm_tile_kernel<BMN, BMN, WGM, WGN, true, true, false, ST>            \
-              : (gemm_fn)gemm_tile_kernel<BMN, BMN, WGM, WGN, true, false, false, ST>)          \
-        : (tb ? (gemm_fn)gemm_tile_kernel<BMN, BMN, WGM, WGN, false, true, false, ST>           \
-              : (gemm_fn)gemm_tile_kernel<BMN, BMN, WGM, WGN, false, false, false, ST>))
-#define LITHOS_TILE_PICK(BMN, WGM, WGN) (st ? LITHOS_TILE_PICK4(BMN, WGM, WGN, true) : LITHOS_TILE_PICK4(BMN, WGM, WGN, false))
-#define LITHOS_TILE_PICK_SPLIT4(BMN, ST)                                                        \
-    (tb ? (gemm_fn)gemm_tile_kernel<BMN, BMN, 2, 2, false, true, true, ST>                      \
-        : (gemm_fn)gemm_tile_kernel<BMN, BMN, 2, 2, false, false, true, ST>)
-#define LITHOS_TILE_PICK_SPLIT(BMN) (st ? LITHOS_TILE_PICK_SPLIT4(BMN, true) : LITHOS_TILE_PICK_SPLIT4(BMN, false))
+    (ta ? (tb ? (gemm_fn)gemm_tile_kernel<BMN, BMN, WGM, WGN, true, true, ST>                   \
+              : (gemm_fn)gemm_tile_kernel<BMN, BMN, WGM, WGN, true, false, ST>)                 \
+        : (tb ? (gemm_fn)gemm_tile_kernel<BMN, BMN, WGM, WGN, false, true, ST>                  \
+              : (gemm_fn)gemm_tile_kernel<BMN, BMN, WGM, WGN, false, false, ST>))
 
 } // namespace lithos
