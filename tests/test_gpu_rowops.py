@@ -246,3 +246,20 @@ def test_gelu_over_its_whole_range():
     d = np.abs(y.cpu().numpy()[0].astype(np.float64) - ref)
     lower = e * (5 + 4 * (1 + 1.26 * np.abs(u64)) + 1.25 * u64 ** 2)
     assert np.all(d <= np.abs(ref) * np.where(u < 0, lower, 5 * e) + 1e-37), np.max(d / np.maximum(np.abs(ref), 1e-37) / e)
+
+
+@pytest.mark.parametrize("n", [77, 1024, 1032, 4096])
+def test_softmax_exponential_is_that_of_single_precision(n):
+    """With one score of 0 and the others below -30 the denominator is 1 in fp32, so the probabilities are the kernel's
+    exponentials.  Error: the hardware's 2^a, one unit in the last place (2^-23), and two roundings of an argument
+    within half a unit (2^-26 each, times ln 2); subnormal results are rounded once more (2^-150)."""
+    rng = np.random.default_rng(n)
+    s = rng.uniform(-87.0, -30.0, (1 << 20) // n * n).astype(np.float32).reshape(-1, n)
+    s[::4] -= 16.0                  # a quarter of the rows down to the last subnormal number
+    s[:, n // 3] = 0.0
+    p = nan_like(s.shape, torch.float32)
+    launch(B.softmax_op(torch.from_numpy(s).cuda(), p, s.shape[0], n, scale=1.0))
+    ref = np.exp(s.astype(np.float64))
+    d = np.abs(p.cpu().numpy().astype(np.float64) - ref)
+    rel = 2.0 ** -23 + 2 * 2.0 ** -26 * math.log(2.0)
+    assert (d <= rel * ref + 2.0 ** -150).all(), np.max((d - 2.0 ** -150) / ref)
