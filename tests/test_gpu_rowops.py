@@ -263,3 +263,21 @@ def test_softmax_exponential_is_that_of_single_precision(n):
     d = np.abs(p.cpu().numpy().astype(np.float64) - ref)
     rel = 2.0 ** -23 + 2 * 2.0 ** -26 * math.log(2.0)
     assert (d <= rel * ref + 2.0 ** -150).all(), np.max((d - 2.0 ** -150) / ref)
+
+
+def test_gelu_is_that_of_single_precision_at_ordinary_arguments():
+    """With e = 2^-24.  u > 0: Phi lies in [1/2, 1), so its last rounding is at most e relative, the product with u as
+    much, and what is added to 1/2 (less than 0.45 of Phi) or subtracted from 1 (less than 0.12 of it) carries the rest:
+    2.5 e.  -1.25 < u < 0: Phi = 1/2 - d, where d carries 1.5 e (the last rounding of P, e/4 absolute or 0.8 e relative, of
+    z and of the coefficients), is subtracted with a rounding of at most e/4 absolute, and the fit is 0.2 e (1.2e-8) of
+    Phi away; the product with u rounds by e."""
+    rng = np.random.default_rng(5)
+    u = np.concatenate([rng.uniform(1e-3, 0.5, 1 << 20), rng.uniform(0.5, 14.0, 1 << 20), -rng.uniform(1e-3, 1.25, 1 << 20)]).astype(np.float32)
+    y = nan_like((1, u.size), torch.float32)
+    launch(B.bias_act_op(torch.from_numpy(u).cuda(), y, 1, u.size, None, gelu=True))
+    from scipy.special import ndtr
+    u64, e = u.astype(np.float64), 2.0 ** -24
+    phi = ndtr(u64)
+    rel = np.abs(y.cpu().numpy()[0].astype(np.float64) / (u64 * phi) - 1.0)
+    bound = np.where(u64 > 0, 2.5 * e, e * (1.2 + (1.5 * (0.5 - phi) + 0.25) / phi))
+    assert (rel <= bound).all(), (np.max(rel[u64 > 0]) / e, np.max(rel / bound))
