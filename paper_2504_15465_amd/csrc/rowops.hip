@@ -270,10 +270,11 @@ __global__ __launch_bounds__(256) void layernorm_kernel(RowArgs a, AtomArgs atom
 }
 
 // Register-resident variant: the row is read ONCE and stays in registers (16 elements per thread) for the
-// mean, the centred variance and the output; needs H <= 16 * TPR.  A thread holds 16 / W runs of W
-// consecutive elements: W = 4 or 8 where H and the pointers permit 16-byte accesses of fp32 or bf16 rows,
-// W = 1 for any H.  Bound by HBM on many rows (16384 x 1024 bf16: 17 us = 4.0 TB/s), by launch and
-// latency on few.
+// mean, the centred variance and the output; needs H <= 16 * TPR and rows that 16-byte accesses fit: a thread holds
+// 16 / W runs of W = 4 (fp32) or 8 (bf16) consecutive elements.  Bound by HBM on many rows (16384 x 1024 bf16: 16.3 us
+// = 4.1 TB/s), by launch and latency on few.  Other rows take the general kernel above: with single elements this form
+// has 16 conditional loads of x, gamma and beta each in a row, and the compiler waits for every one where it is issued
+// (16384 x 1025 bf16: 151 us against 46, 16384 x 127: 25 against 10).
 template <bool IN32, bool OUT32, int TPR, int W>
 __global__ __launch_bounds__(256) void layernorm_vec_kernel(RowArgs a, AtomArgs atom)
 {
@@ -580,7 +581,7 @@ typedef void (*row_fn)(RowArgs, AtomArgs);
 #define PICK3W(K, T, W) (in32 ? (out32 ? (row_fn)K<true, true, T, W> : (row_fn)K<true, false, T, W>) : (out32 ? (row_fn)K<false, true, T, W> : (row_fn)K<false, false, T, W>))
 #define PICKROW(K)                                                                                                    \
     (variant == RV_WIDE ? (wide ? (row_fn)K<false, false, 256, 8> : (row_fn)K<false, false, 64, 8>)                   \
-                        : variant == RV_VEC4 ? (wide ? PICK3W(K, 256, 4) : PICK3W(K, 64, 4)) : (wide ? PICK3W(K, 256, 1) : PICK3W(K, 64, 1)))
+                        : (wide ? PICK3W(K, 256, 4) : PICK3W(K, 64, 4)))
 static row_fn row_kernel(const lithos_op_t& op, int variant)
 {
     const bool in32 = op.flags & LITHOS_F_IN_F32, out32 = op.flags & LITHOS_F_OUT_F32;
@@ -598,6 +599,7 @@ static row_fn row_kernel(const lithos_op_t& op, int variant)
         if (variant == 1) return wide ? PICK3(rmsnorm_vec_kernel, 256) : PICK3(rmsnorm_vec_kernel, 64);
         return wide ? PICK3(rmsnorm_kernel, 256) : PICK3(rmsnorm_kernel, 64);
     case LITHOS_OP_SOFTMAX:
+        if (variant == RV_SCALAR) return wide ? PICK3W(softmax_vec_kernel, 256, 1) : PICK3W(softmax_vec_kernel, 64, 1);
         if (variant) return PICKROW(softmax_vec_kernel);
         return wide ? PICK3(softmax_kernel, 256) : PICK3(softmax_kernel, 64);
     case LITHOS_OP_ROPE_KV: return in32 ? (row_fn)rope_kv_kernel<true> : (row_fn)rope_kv_kernel<false>;
@@ -652,6 +654,7 @@ int rowops_plan(const lithos_op_t& op, OpPlan* plan)
         blocks = (rows + (256 / tpr_for(cols)) - 1) / (256 / tpr_for(cols));
         plan->variant = row_variant(op, aligned16(op.in[0]) && aligned16(op.in[1]) && aligned16(op.in[2]) && aligned16(op.out[0]) &&
                                             (!op.out[1] || aligned16(op.out[1])));
+        if (plan->variant == RV_SCALAR) plan->variant = RV_ANY;     // slower than several passes, see layernorm_vec_kernel
         break;
     case LITHOS_OP_RMSNORM:
         if (!op.in[1] || !op.out[0]) return fail(LITHOS_EINVAL, "rmsnorm: null weight or output");

@@ -281,3 +281,20 @@ def test_gelu_is_that_of_single_precision_at_ordinary_arguments():
     rel = np.abs(y.cpu().numpy()[0].astype(np.float64) / (u64 * phi) - 1.0)
     bound = np.where(u64 > 0, 2.5 * e, e * (1.2 + (1.5 * (0.5 - phi) + 0.25) / phi))
     assert (rel <= bound).all(), (np.max(rel[u64 > 0]) / e, np.max(rel / bound))
+
+
+def median_us(op):
+    """Median launch time, the best of three rounds."""
+    torch.cuda.synchronize()
+    return min(B.lithos_time_launch(ctx(), op, 0, None, 3, 15)[1] for _ in range(3))
+
+
+@pytest.mark.parametrize("cols,most", [(127, 1.8), (1025, 4.0), (4095, 4.0)])
+def test_layernorm_of_odd_rows_costs_no_more_than_its_passes(cols, most):
+    """Rows that no wide access fits are read three times in single elements; the next longer rows are read once
+    (measured: 1.1, 1.8 and 2.2 times as long; 2.6, 6.0 and 6.4 in the register-resident form of single elements)."""
+    rows = 16384
+    x = torch.randn(rows * (cols + 7), device="cuda").to(torch.bfloat16)
+    y, g = torch.empty_like(x), torch.randn(cols + 7, device="cuda")
+    t = [median_us(B.layernorm_op(x, g, g, y, rows, c)) for c in (cols, (cols + 7) // 8 * 8)]
+    assert t[0] <= most * t[1], t
