@@ -666,6 +666,10 @@ int rowops_plan(const lithos_op_t& op, OpPlan* plan)
         if (!op.out[0]) return fail(LITHOS_EINVAL, "softmax: null output");
         blocks = (rows + (256 / tpr_for(cols)) - 1) / (256 / tpr_for(cols));
         plan->variant = row_variant(op, aligned16(op.in[0]) && aligned16(op.out[0]));
+        // Short rows leave most of the 16 elements per thread idle, and the general kernel's further reads hit the cache:
+        // 131072 rows of bf16, registers / general: 33 columns 49 / 35 us, 64 46 / 36, 72 46 / 46, 128 46 / 52, 512 49 / 145;
+        // in single elements 77 columns 51 / 47, 127 51 / 50, 129 54 / 61.
+        if (cols <= (plan->variant == RV_SCALAR ? 128 : 64)) plan->variant = RV_ANY;
         break;
     case LITHOS_OP_ROPE_KV: {
         // dim = rows, n_q, n_kv, d, pos, cap

@@ -203,7 +203,7 @@ def test_row_ops_refuse_bad_arguments():
         assert e.value.code == B.EINVAL
 
 
-@pytest.mark.parametrize("rows,cols", [(1, 1), (5, 3), (9, 8), (6, 12), (3, 63), (130, 64), (4, 1023), (5, 1024), (3, 1025), (2, 1032),
+@pytest.mark.parametrize("rows,cols", [(1, 1), (5, 3), (9, 8), (6, 12), (3, 63), (130, 64), (70, 65), (66, 72), (5, 127), (3, 129), (4, 1023), (5, 1024), (3, 1025), (2, 1032),
                                        (3, 4095), (2, 4096), (2, 4097), (2, 4104)])
 @pytest.mark.parametrize("in32,out32", [(False, False), (True, True), (True, False)])
 def test_row_kernels_at_the_edges_of_their_variants(rows, cols, in32, out32):
@@ -298,3 +298,12 @@ def test_layernorm_of_odd_rows_costs_no_more_than_its_passes(cols, most):
     y, g = torch.empty_like(x), torch.randn(cols + 7, device="cuda")
     t = [median_us(B.layernorm_op(x, g, g, y, rows, c)) for c in (cols, (cols + 7) // 8 * 8)]
     assert t[0] <= most * t[1], t
+
+
+def test_softmax_of_short_rows_costs_less_than_of_longer_ones():
+    """A row of 33 scores is an eighth of one of 264 (measured: 0.76 of its time; 1.06 in the register-resident form)."""
+    rows = 131072
+    x = torch.randn(rows * 264, device="cuda").to(torch.bfloat16)
+    y = torch.empty_like(x)
+    t = [median_us(B.softmax_op(x, y, rows, c)) for c in (33, 264)]
+    assert t[0] <= 0.91 * t[1], t
