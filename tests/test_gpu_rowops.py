@@ -307,3 +307,13 @@ def test_softmax_of_short_rows_costs_less_than_of_longer_ones():
     y = torch.empty_like(x)
     t = [median_us(B.softmax_op(x, y, rows, c)) for c in (33, 264)]
     assert t[0] <= 0.91 * t[1], t
+
+
+def test_bias_of_odd_rows_stays_near_the_wide_form():
+    """Single elements against 16-byte accesses of nearly the same bytes (measured: 1.3 times as long; 1.8 with every
+    load waited for by itself)."""
+    rows = 16384
+    x, b = torch.randn(rows * 1024, device="cuda").to(torch.bfloat16), torch.randn(1024, device="cuda")
+    y = torch.empty_like(x)
+    t = [median_us(B.bias_act_op(x, y, rows, c, b, gelu=False)) for c in (1023, 1024)]
+    assert t[0] <= 1.6 * t[1], t
