@@ -72,13 +72,46 @@ __device__ __forceinline__ void epilogue_store(const GemmArgs& g, int m, int n, 
     }
 }
 
-// The same value without the store, for the epilogue that goes through LDS (m, n in range).
-__device__ __forceinline__ uint16_t epilogue_bf16(const GemmArgs& g, int m, int n, float v)
+// One finished value of C.
+__device__ __forceinline__ void store_value(const GemmArgs& g, int64_t i, float v)
 {
-    if (g.flags & LITHOS_F_BIAS) v += g.bias[n];
-    if (g.flags & LITHOS_F_GELU) v = gelu_erf(v);
-    if (g.flags & LITHOS_F_RESIDUAL) v += g.resid[(int64_t)m * g.ldr + n];
-    return f32_to_bf16(v);
+    if (g.flags & LITHOS_F_OUT_F32) {
+        reinterpret_cast<float*>(g.C)[i] = v;
+    } else {
+        uint16_t hi = f32_to_bf16(v);
+        reinterpret_cast<uint16_t*>(g.C)[i] = hi;
+        if (g.flags & LITHOS_F_OUT_SPLIT)       // second bf16 carries what the first one dropped
+            reinterpret_cast<uint16_t*>(g.C)[g.c_plane + i] = f32_to_bf16(v - bf16_to_f32(hi));
+    }
+}
+
+// An accumulator block whose elements leave one by one: element e of the lane is (m, n) moved by 8*(e/4) + e%4 rows, or
+// columns with exchanged operands.  The bits of epilogue_store, but all loads of bias and residual come before the first
+// store (the compiler may not move a load of the residual above a store of C, and a round trip for each element is what a
+// ragged tile's time consisted of), and a block inside the matrix is stored without a test per element.  Elements beyond
+// the matrix compute on its last row and column and are not stored.
+template <bool SWAPPED>
+__device__ __forceinline__ void epilogue_store_block(const GemmArgs& g, int m, int n, f32x16 v, bool inside)
+{
+    const auto row = [&](int e) { return SWAPPED ? m : m + 8 * (e >> 2) + (e & 3); };
+    const auto col = [&](int e) { return SWAPPED ? n + 8 * (e >> 2) + (e & 3) : n; };
+    const bool with_bias = g.flags & LITHOS_F_BIAS, with_resid = g.flags & LITHOS_F_RESIDUAL;      // uniform
+    float bv[16], rv[16];
+    if (with_bias) static_for<16>([&](auto ee) { constexpr int e = decltype(ee)::value; bv[e] = g.bias[min(col(e), g.N - 1)]; });
+    if (with_resid)
+        static_for<16>([&](auto ee) { constexpr int e = decltype(ee)::value; rv[e] = g.resid[min(row(e), g.M - 1) * g.ldr + min(col(e), g.N - 1)]; });
+    if (with_bias) static_for<16>([&](auto ee) { constexpr int e = decltype(ee)::value; v[e] += bv[e]; });
+    if (g.flags & LITHOS_F_GELU) static_for<16>([&](auto ee) { constexpr int e = decltype(ee)::value; v[e] = gelu_erf(v[e]); });
+    if (with_resid) static_for<16>([&](auto ee) { constexpr int e = decltype(ee)::value; v[e] += rv[e]; });
+    const int64_t first = m * g.ldc + n, step = SWAPPED ? 1 : g.ldc;
+    if (inside) {
+        static_for<16>([&](auto ee) { constexpr int e = decltype(ee)::value; store_value(g, first + (8 * (e >> 2) + (e & 3)) * step, v[e]); });
+    } else {
+        static_for<16>([&](auto ee) {
+            constexpr int e = decltype(ee)::value;
+            if (row(e) < g.M && col(e) < g.N) store_value(g, first + (8 * (e >> 2) + (e & 3)) * step, v[e]);
+        });
+    }
 }
 
 // ---- epilogue of a full bf16 tile through LDS ---------------------------------

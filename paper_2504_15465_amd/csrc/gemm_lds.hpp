@@ -262,7 +262,7 @@ void gemm_lds_kernel(GemmArgs g, AtomArgs atom)
                                         n0 + wn * WN + j * 32, acc[i][j], lane);
             });
         } else if (wide) {
-            // rows 0 .. BM/2-1 of the bf16 tile are staged in A0, the others in B0 (64x64: all in A0)
+            // rows 0 .. HALF-1 of the bf16 tile are staged in A0, the others in hi_half
             constexpr int PPR = BN / 8, HALF = BM == 64 ? 64 : BM / 2;
             static_assert(KG * AP * AE >= HALF * BN && (BM == 64 || (S == 3 ? KG * AP * AE : KG * BE) >= HALF * BN), "staged output");
             uint16_t* const C = reinterpret_cast<uint16_t*>(g.C);
@@ -295,7 +295,7 @@ void gemm_lds_kernel(GemmArgs g, AtomArgs atom)
         } else if (grp == 0) {
             static_for<MI * NI>([&](auto ij) {
                 constexpr int i = decltype(ij)::value / NI, j = decltype(ij)::value % NI;
-                store_block_swapped(g, m0 + wm * WM + i * 32 + (lane & 31), n0 + wn * WN + j * 32, acc[i][j], lane);
+                epilogue_store_block<true>(g, m0 + wm * WM + i * 32 + (lane & 31), n0 + wn * WN + j * 32 + 4 * (lane >> 5), acc[i][j], false);
             });
         }
         return;
@@ -304,14 +304,10 @@ void gemm_lds_kernel(GemmArgs g, AtomArgs atom)
     if (grp != 0) return;
     // 32x32 accumulator block: lane holds column (lane & 31); element e is
     // row 8*(e/4) + 4*(lane/32) + e%4.
+    const bool inside = m0 + BM <= g.M && n0 + BN <= g.N;
     static_for<MI * NI>([&](auto ij) {
         constexpr int i = decltype(ij)::value / NI, j = decltype(ij)::value % NI;
-        const int n = n0 + wn * WN + j * 32 + (lane & 31);
-        const int mb = m0 + wm * WM + i * 32 + 4 * (lane >> 5);
-        static_for<16>([&](auto ee) {
-            constexpr int e = decltype(ee)::value;
-            epilogue_store(g, mb + 8 * (e >> 2) + (e & 3), n, acc[i][j][e]);
-        });
+        epilogue_store_block<false>(g, m0 + wm * WM + i * 32 + 4 * (lane >> 5), n0 + wn * WN + j * 32 + (lane & 31), acc[i][j], inside);
     });
 }
 

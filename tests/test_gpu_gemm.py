@@ -682,3 +682,53 @@ def test_pipelined_tiles_at_every_remainder_of_k(tile, split, k):
             assert np.abs(c.cpu().numpy().astype(np.float64) - full).max() <= bound
         else:
             bf16_close(c, full, abs_tol=bound)
+
+
+@pytest.mark.parametrize("tile,split", [(64, False), (64, True), (128, False), (128, True)])
+@pytest.mark.parametrize("extra,padded", [(3, False), (3, True), (4, False), (4, True), (8, False)])
+def test_columns_that_leave_element_by_element(tile, split, extra, padded):
+    """N that no whole 16-byte pieces make up, in rows of C that 16-byte pieces fit (padded to a multiple of 8: the inner
+    tiles go through LDS, the last column of tiles element by element) and in rows that they do not (every tile element by
+    element); fp32, bf16 and paired bf16 C, with bias, GELU and residual (their rows unaligned) and without.
+    Error of the fp32 sum at most K * 2^-24 of the sum of magnitudes (K / 4 for uniform operands), GELU steepens it by at most 1.13."""
+    m, n, k = tile + 5, tile + extra, 200
+    ldc = (n + 7) // 8 * 8 + 8 if padded else n
+    a_bits, b_bits = inputs.gemm_operands(m, n, k, seed=tile + extra, tb=True)
+    a, b = dev_bits(a_bits), dev_bits(b_bits)
+    acc = O.gemm(a_bits, b_bits, tb=True)
+    if split:       # lo plane = hi plane scaled by 2^-8: exactly representable
+        a = torch.stack([a, (a.float() * 2.0 ** -8).to(torch.bfloat16)]).contiguous()
+        acc = acc * (1.0 + 2.0 ** -8)
+    pad = torch.randn(n + 1 + m * (n + 1) + 1, device="cuda")
+    bias, resid = pad[1:n + 1], pad[n + 2:].view(m, n + 1)[:, :n]
+    full = O.bias_act(acc, bias.double().cpu().numpy(), gelu=True) + resid.double().cpu().numpy()
+    bound = 1.13 * (2.0 ** -24 * k * (k / 4 + 1) + 2.0 ** -19)
+    for epi, ref in ((dict(), acc), (dict(bias=bias, gelu=True, residual=resid, ldr=n + 1), full)):
+        for dt, pair in ((torch.float32, False), (torch.bfloat16, False), (torch.bfloat16, True)):
+            outs = []
+            for atom_blocks in (0, 2):
+                c = nan_like((2 if pair else 1, m, ldc), dt)
+                _launch(B.gemm_op(a, b, c, m, n, k, tb=True, tile=tile, a_split=split, c_split=pair, ldc=ldc, **epi), atom_blocks)
+                assert torch.isnan(c[:, :, n:].float()).all() and not torch.isnan(c[:, :, :n].float()).any()
+                outs.append(c)
+            assert bits_equal(outs[0], outs[1])
+            got = outs[0][0, :, :n]
+            if dt is torch.float32:
+                assert np.abs(got.double().cpu().numpy() - ref).max() <= bound
+            else:
+                bf16_close(got, ref, abs_tol=bound)
+                if pair:
+                    both = got.double() + outs[0][1, :, :n].double()
+                    assert np.abs(both.cpu().numpy() - ref).max() <= 2.0 ** -16 * np.abs(ref).max() + bound
+
+
+def test_epilogue_of_ragged_tiles_costs_little():
+    """Rows of C that no wide store fits, with and without bias, GELU and residual (1.4 times as long; 2.4 when every
+    element waits for its residual)."""
+    m, n, k = 1003, 3001, 1160
+    a, b = torch.randn((m, k), device="cuda").to(torch.bfloat16), torch.randn((n, k), device="cuda").to(torch.bfloat16)
+    c, bias, resid = nan_like((m, n), torch.bfloat16), torch.randn(n, device="cuda"), torch.randn((m, n), device="cuda")
+    torch.cuda.synchronize()
+    t = [min(B.lithos_time_launch(ctx(), B.gemm_op(a, b, c, m, n, k, tb=True, tile=128, **e), 0, None, 3, 15)[1] for _ in range(3))
+         for e in (dict(bias=bias, gelu=True, residual=resid), dict())]
+    assert t[0] <= 1.9 * t[1], t
