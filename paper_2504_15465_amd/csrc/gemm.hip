@@ -26,7 +26,7 @@ namespace lithos {
 
 // ---- host side -------------------------------------------------------------
 
-static int tile_threads(int variant) { return variant == V_TILE128 ? 256 : 512; }
+static int tile_threads(int variant) { return variant == V_TILE64 || variant == V_TILE128 ? 256 : 512; }
 
 // full bf16 tiles can leave through LDS when whole 16-byte pieces of C rows are addressable
 // (fp32 tiles of the same kernels are stored from registers, 16 bytes per lane)
@@ -43,7 +43,8 @@ static gemm_fn variant_fn(int variant, bool ta, bool tb, bool a32, bool split, b
 {
     switch (variant) {
     case V_LDS256: return st ? gemm_lds256_wide_fn(ta, tb) : gemm_lds256_elem_fn(ta, tb);
-    case V_TILE64: return gemm_tile64_fn(ta, tb, split, st);
+    case V_TILE64: return gemm_tile64_fn(ta, tb, split, st, false);
+    case V_TILE64_2K: return gemm_tile64_fn(ta, tb, split, st, true);
     case V_TILE128: return gemm_tile128_fn(ta, tb, split, st);
     case V_TILE256: return st ? gemm_tile256_wide_fn(ta, tb) : gemm_tile256_elem_fn(ta, tb);
     default: return gemm_skinny_fn(variant, a32, norm);
@@ -122,6 +123,14 @@ int gemm_plan(const lithos_op_t& op, OpPlan* plan)
         variant = tile == 64 ? V_TILE64 : tile == 128 ? V_TILE128 : V_TILE256;
         if (tile == 256 && K % 64 == 0) variant = V_LDS256;
         plan->grid = {(uint32_t)((N + tile - 1) / tile), (uint32_t)((M + tile - 1) / tile), (uint32_t)(slices > 1 ? slices : 1)};
+        // The 64 tile splits K between two groups of wavefronts while all blocks of the whole grid (never of an atom: the
+        // sums must not depend on the cut) find room at two per CU of the whole chip: then the chain of k-tiles is the
+        // time (us, two groups / one: 1024 x 1024 x 8192 NN 47 / 65, split 128 x 768 x 3072 19 / 22).  More blocks hide it,
+        // and the second group only waits in the prologue and epilogue (8192 x 1024 x 512 NT 25 / 21, 4096 x 4096 x 64
+        // 29 / 17, 4096^3 NN 240 / 211, split 4096 x 768 x 3072 59 / 52), up to chains so long that more blocks in
+        // flight cost more in L2 than they hide (8192^3 TN 1661 / 2204, NN 1711 / 1708).
+        const uint64_t blocks = (uint64_t)plan->grid.x * plan->grid.y * plan->grid.z;
+        if (tile == 64 && (blocks <= 512 || (!split && K / plan->grid.z > 4096))) variant = V_TILE64_2K;
     } else {
         return fail(LITHOS_EINVAL, "gemm: unknown tile selector %d", tile);
     }

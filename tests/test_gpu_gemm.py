@@ -732,3 +732,46 @@ def test_epilogue_of_ragged_tiles_costs_little():
     t = [min(B.lithos_time_launch(ctx(), B.gemm_op(a, b, c, m, n, k, tb=True, tile=128, **e), 0, None, 3, 15)[1] for _ in range(3))
          for e in (dict(bias=bias, gelu=True, residual=resid), dict())]
     assert t[0] <= 1.9 * t[1], t
+
+
+@pytest.mark.parametrize("split", [False, True])
+@pytest.mark.parametrize("ta,tb,m,n,k,slices", [
+    (False, False, 1024, 2048, 72, 0),      # 512 blocks: two groups of wavefronts
+    (False, True, 1025, 2051, 136, 0),      # 561 blocks, ragged everywhere: one group
+    (False, False, 1480, 1480, 8, 0),       # 576 blocks, one k-tile of 8
+    (True, False, 512, 584, 1000, 8),       # 640 blocks in 8 K slices
+    (True, True, 1480, 1485, 64, 0),
+    (False, True, 1470, 1480, 4168, 0),     # 552 blocks with a long chain: two groups (one with a split A)
+])
+def test_64_tile_with_one_and_two_groups_of_wavefronts(ta, tb, m, n, k, slices, split):
+    """Both sides of the rule by the number of blocks, in every layout: against the oracle, and the same bits however the
+    launch is cut.  fp32 sums: at most K * 2^-24 of the sum of magnitudes (K / 4 for uniform operands)."""
+    if split and (ta or slices):
+        pytest.skip("a split A is not transposed; slices as without")
+    a_bits, b_bits = inputs.gemm_operands(m, n, k, seed=k + m, ta=ta, tb=tb)
+    a, b = dev_bits(a_bits), dev_bits(b_bits)
+    ref = O.gemm(a_bits, b_bits, ta=ta, tb=tb)
+    if split:
+        a = torch.stack([a, (a.float() * 2.0 ** -8).to(torch.bfloat16)]).contiguous()
+        ref = ref * (1.0 + 2.0 ** -8)
+    outs = []
+    for atom_blocks in (0, 100):
+        c = nan_like((max(1, slices), m, n), torch.float32)
+        _launch(B.gemm_op(a, b, c, m, n, k, ta=ta, tb=tb, tile=64, a_split=split, k_slices=slices), atom_blocks)
+        outs.append(c)
+    assert bits_equal(outs[0], outs[1])
+    assert np.abs(outs[0].double().sum(0).cpu().numpy() - ref).max() <= 2.0 ** -24 * k * (k / 4 + 1)
+    if not slices:
+        c16 = nan_like((m, n), torch.bfloat16)
+        _launch(B.gemm_op(a, b, c16, m, n, k, ta=ta, tb=tb, tile=64, a_split=split))
+        assert torch.equal(c16, outs[0][0].to(torch.bfloat16))
+
+
+def test_64_tile_of_many_blocks_stays_near_the_128_tile_on_a_short_chain():
+    """4096 blocks of one k-tile: prologue and epilogue are the time (1.14 of the 128 tile's; 1.94 with two groups)."""
+    n, k = 4096, 64
+    a, b = torch.randn((n, k), device="cuda").to(torch.bfloat16), torch.randn((n, k), device="cuda").to(torch.bfloat16)
+    c = nan_like((n, n), torch.bfloat16)
+    torch.cuda.synchronize()
+    t = [min(B.lithos_time_launch(ctx(), B.gemm_op(a, b, c, n, n, k, tb=True, tile=tile), 0, None, 3, 15)[1] for _ in range(3)) for tile in (64, 128)]
+    assert t[0] <= 1.45 * t[1], t
