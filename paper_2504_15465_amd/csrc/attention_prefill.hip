@@ -13,9 +13,11 @@
 //                 as it lies in memory, [key][d], and its fragments come out of the
 //                 transposing LDS load (ds_read_b64_tr_b16), so nothing is transposed by hand.
 // The key and value blocks go from global memory straight into one of two LDS stages
-// (global_load_lds_dwordx4) a block ahead, with one barrier per block; all four wavefronts read them.  (Through
-// registers and one stage, two barriers per block: 612 us for 8192 tokens, 32/8 heads; this form 587 us, 937 TFLOP/s.
-// Bound now by the softmax's vector arithmetic, the LDS reads and the MFMAs, each busy less than half the time.)  Probabilities are rounded to bf16 for the second
+// (global_load_lds_dwordx4) a block ahead, with one barrier per block; all four wavefronts read them.  8192 tokens, 32/8
+// heads: 575 us, 956 TFLOP/s (through registers and one stage, two barriers per block: 643).  Raising the priority of the wavefronts
+// in their MFMAs (s_setprio) costs 3 to 5 % with two stages, on 256 and on 64 CUs alike, and the
+// high-priority neighbours of this best-effort kernel wait longer: p99 of an MLP request beside 16384 tokens 699 us
+// against 675.  Probabilities are rounded to bf16 for the second
 // product; the normalisation is applied to the fp32 result.
 //
 // The tile a workgroup computes is named by its LOGICAL block index (LithOS Section 4.4), so
@@ -114,8 +116,6 @@ __global__ __launch_bounds__(256, 2) void attn_prefill_kernel(PrefillArgs a, Ato
     auto block = [&](const uint16_t* Ks, const uint16_t* Vs, int kb) {
         const int key_base = kb * PF_KB;
         if (key_base > q0 + 31) return;                     // every key of the block lies after this wavefront's queries
-        // the wavefront that multiplies goes before the one in its softmax: 8192 tokens 633 -> 612 us
-        __builtin_amdgcn_s_setprio(1);
         pf_f32x16 s[2];
         bool live[2];
 #pragma unroll
@@ -131,7 +131,6 @@ __global__ __launch_bounds__(256, 2) void attn_prefill_kernel(PrefillArgs a, Ato
                 }
             }
         }
-        __builtin_amdgcn_s_setprio(0);
         // accumulator element e of sub-block `sub` is key key_base + 32 sub + 8 (e/4) + 4 half + e%4
         const bool diag = key_base + PF_KB - 1 > q0;        // some key of the block lies after some query
         // The running maximum is kept in raw score units; the scale (times log2 e) enters as the
@@ -181,7 +180,6 @@ __global__ __launch_bounds__(256, 2) void attn_prefill_kernel(PrefillArgs a, Ato
         // 32 sub + 16 gp + 8 (j/4) + 4 half + j%4 = accumulator element 8 gp + j of s[sub]; the V
         // fragment of that step holds the same eight keys: two transposing loads, four keys each.
         const int grp = lane >> 4, sl = lane & 15;
-        __builtin_amdgcn_s_setprio(1);
 #pragma unroll
         for (int sub = 0; sub < 2; ++sub) {
             if (!live[sub]) continue;
@@ -203,7 +201,6 @@ __global__ __launch_bounds__(256, 2) void attn_prefill_kernel(PrefillArgs a, Ato
                 }
             }
         }
-        __builtin_amdgcn_s_setprio(0);
     };
     // this wavefront's pieces of the next block have landed and its LDS reads are done; then everybody's
     auto turn = [&]() {
