@@ -52,14 +52,17 @@ __device__ __forceinline__ int pf_k_index(int key, int chunk) { return key * PF_
 // transposing load touches fall into different banks.
 __device__ __forceinline__ int pf_v_index(int key, int d) { return key * PF_D + ((((d >> 3) ^ ((key & 3) << 2))) << 3) + (d & 7); }
 
+// DIRECT: the two LDS stages described above.  Without: a block's keys and values wait in registers for one stage, with two
+// barriers per block (see attn_prefill_plan).
+template <bool DIRECT>
 __global__ __launch_bounds__(256, 2) void attn_prefill_kernel(PrefillArgs a, AtomArgs atom)
 {
     // separate arrays, each addressed statically: the compiler can then tell that the LDS reads of one stage do
     // not depend on the loads in flight into the other
     __shared__ __attribute__((aligned(1024))) uint16_t K0[PF_KB * PF_D];
-    __shared__ __attribute__((aligned(1024))) uint16_t K1[PF_KB * PF_D];
+    __shared__ __attribute__((aligned(1024))) uint16_t K1[DIRECT ? PF_KB * PF_D : 8];
     __shared__ __attribute__((aligned(1024))) uint16_t V0[PF_KB * PF_D];
-    __shared__ __attribute__((aligned(1024))) uint16_t V1[PF_KB * PF_D];
+    __shared__ __attribute__((aligned(1024))) uint16_t V1[DIRECT ? PF_KB * PF_D : 8];
 
     const uint32_t L = atom_logical_block(atom);
     // A block computes TWO query tiles, number p from the end of the prompt and number p from its
@@ -202,20 +205,45 @@ __global__ __launch_bounds__(256, 2) void attn_prefill_kernel(PrefillArgs a, Ato
             }
         }
     };
-    // this wavefront's pieces of the next block have landed and its LDS reads are done; then everybody's
-    auto turn = [&]() {
-        __builtin_amdgcn_s_waitcnt(0x0070);                 // vmcnt(0) lgkmcnt(0)
-        __syncthreads();
-    };
-    fetch(K0, V0, 0);
-    turn();
-    for (int kb = 0; kb < nkb; kb += 2) {                   // a tile sees an even number of blocks
-        fetch(K1, V1, kb + 1);
-        block(K0, V0, kb);
+    if constexpr (DIRECT) {
+        // this wavefront's pieces of the next block have landed and its LDS reads are done; then everybody's
+        auto turn = [&]() {
+            __builtin_amdgcn_s_waitcnt(0x0070);             // vmcnt(0) lgkmcnt(0)
+            __syncthreads();
+        };
+        fetch(K0, V0, 0);
         turn();
-        if (kb + 2 < nkb) fetch(K0, V0, kb + 2);
-        block(K1, V1, kb + 1);
-        turn();
+        for (int kb = 0; kb < nkb; kb += 2) {               // a tile sees an even number of blocks
+            fetch(K1, V1, kb + 1);
+            block(K0, V0, kb);
+            turn();
+            if (kb + 2 < nkb) fetch(K0, V0, kb + 2);
+            block(K1, V1, kb + 1);
+            turn();
+        }
+    } else {
+        // 1024 chunks of 16 bytes per operand, four per thread, in registers of their own (an array that lives across the
+        // loop's back edge is placed in scratch memory by the compiler)
+        uint4 k0, k1, k2, k3, v0, v1, v2, v3;
+        auto load = [&](int i, int kb, uint4& kr, uint4& vr) {
+            const int c = tid + 256 * i;
+            const int64_t off = (int64_t)(kb * PF_KB + (c >> 4)) * tok + (c & 15) * 8;
+            kr = *reinterpret_cast<const uint4*>(kg + off);
+            vr = *reinterpret_cast<const uint4*>(vg + off);
+        };
+        auto stash = [&](int i, const uint4& kr, const uint4& vr) {
+            const int c = tid + 256 * i, key = c >> 4, ch = c & 15;
+            *reinterpret_cast<uint4*>(K0 + pf_k_index(key, ch)) = kr;
+            *reinterpret_cast<uint4*>(V0 + pf_v_index(key, ch * 8)) = vr;
+        };
+        load(0, 0, k0, v0); load(1, 0, k1, v1); load(2, 0, k2, v2); load(3, 0, k3, v3);
+        for (int kb = 0; kb < nkb; ++kb) {
+            __syncthreads();                                // everybody is done reading the previous block
+            stash(0, k0, v0); stash(1, k1, v1); stash(2, k2, v2); stash(3, k3, v3);
+            __syncthreads();
+            if (kb + 1 < nkb) { load(0, kb + 1, k0, v0); load(1, kb + 1, k1, v1); load(2, kb + 1, k2, v2); load(3, kb + 1, k3, v3); }
+            block(K0, V0, kb);
+        }
     }
 
     // o[db][e] is d = 32 db + 8 (e/4) + 4 half + e%4 of query qi; both halves hold half of the denominator
@@ -253,8 +281,10 @@ int attn_prefill_plan(const lithos_op_t& op, OpPlan* plan)
     plan->grid = {(uint32_t)(n_q / n_kv * (T / PF_QT / 2)), (uint32_t)n_kv, (uint32_t)batch};
     plan->total = (uint32_t)total;
     plan->threads = 256;
-    plan->variant = 0;
-    plan->wg_per_cu = cached_occupancy((const void*)attn_prefill_kernel, 256, 2);
+    // Few blocks per tile: the path straight into LDS has the longer latency, and one workgroup per CU does not hide it.
+    // us, registers / two stages, on 256 CUs: 256 tokens 17.8 / 20.0, 512 24.0 / 25.4, 1024 38.0 / 37.0, 2048 68.6 / 64.0.
+    plan->variant = T > 512;
+    plan->wg_per_cu = cached_occupancy(plan->variant ? (const void*)attn_prefill_kernel<true> : (const void*)attn_prefill_kernel<false>, 256, 2);
     return LITHOS_OK;
 }
 
@@ -268,7 +298,7 @@ int attn_prefill_launch(const lithos_op_t& op, const OpPlan& plan, const AtomArg
     a.batch = (int)op.dim[0]; a.n_q = (int)op.dim[1]; a.n_kv = (int)op.dim[2]; a.T = (int)op.dim[4]; a.cap = (int)op.dim[5];
     a.ldq = op.ld[0]; a.ldo = op.ld[1];
     a.scale_log2e = op.fparam[0] * 1.44269504088896340736f;
-    LITHOS_HIP(launch_kernel(attn_prefill_kernel, dim3(LITHOS_ATOM_LAUNCH_BLOCKS(atom)), dim3(plan.threads), s, a, atom));
+    LITHOS_HIP(launch_kernel(plan.variant ? attn_prefill_kernel<true> : attn_prefill_kernel<false>, dim3(LITHOS_ATOM_LAUNCH_BLOCKS(atom)), dim3(plan.threads), s, a, atom));
     return LITHOS_OK;
 }
 
