@@ -126,7 +126,8 @@ def test_exactly_representable_data_matches_oracle_bit_for_bit():
                                        (256, False, 320), (256, True, 320), (256, False, 264)])
 def test_fused_epilogue_bias_gelu_residual(tile, tb, k):
     """Bias, GELU and residual in the epilogue, fp32 and bf16 C; full tiles (through LDS, or 16 bytes per
-    lane for fp32) and ragged edge tiles (element by element) must agree with the oracle alike."""
+    lane for fp32) and ragged edge tiles (N % 8 == 0 here: the same way in the 64 and 128 tiles, element by element in
+    the 256 tiles) must agree with the oracle alike."""
     m, n = (24, 200) if tile == B.TILE_SKINNY else (136, 200) if tile < 256 else (520, 776)
     a_bits, b_bits = inputs.gemm_operands(m, n, k, seed=9, tb=tb)
     bias = inputs.normal_f32((n,), 10, 0.5)
@@ -592,8 +593,8 @@ def test_training_shapes_full_size_sampled_rows():
 
 @pytest.mark.parametrize("tile,k", [(128, 320), (256, 320), (256, 264)])
 def test_split_bf16_output_of_plain_bf16_gemm(tile, k):
-    """C written as a hi + lo bf16 pair by the kernels that take ordinary bf16 operands (full tiles through
-    LDS in two passes where the kernel has that path, ragged tiles element by element): the hi plane is the
+    """C written as a hi + lo bf16 pair by the kernels that take ordinary bf16 operands (through LDS in two
+    passes where the kernel has that path; of the 256 tiles the ragged ones element by element): the hi plane is the
     single-plane result bit for bit, hi + lo carries ~16 significant bits."""
     m, n = 520, 776
     a_bits, b_bits = inputs.gemm_operands(m, n, k, seed=61)
@@ -775,3 +776,39 @@ def test_64_tile_of_many_blocks_stays_near_the_128_tile_on_a_short_chain():
     torch.cuda.synchronize()
     t = [min(B.lithos_time_launch(ctx(), B.gemm_op(a, b, c, n, n, k, tb=True, tile=tile), 0, None, 3, 15)[1] for _ in range(3)) for tile in (64, 128)]
     assert t[0] <= 1.45 * t[1], t
+
+
+def _padded(bits, cols):
+    """The matrix on the device with rows of `cols` elements, NaN behind each and in one more row below; its row stride."""
+    t = nan_like((bits.shape[0] + 1, cols), torch.bfloat16)
+    t[:bits.shape[0], :bits.shape[1]] = dev_bits(bits)
+    return t
+
+
+@pytest.mark.parametrize("tile,split", [(64, False), (64, True), (128, False), (128, True)])
+@pytest.mark.parametrize("ta,tb", [(False, False), (False, True), (True, False), (True, True)])
+@pytest.mark.parametrize("k", [8, 72, 200])
+def test_padding_between_rows_is_never_used(tile, split, ta, tb, k):
+    """Operands and C inside larger buffers: NaN behind every row of A and B and in the row below reaches no result
+    (tiles read past K and past the last row from elsewhere), and the padding of C stays as it was.
+    fp32 sums: at most K * 2^-24 of the sum of magnitudes (K / 4 for uniform operands)."""
+    if split and ta:
+        pytest.skip("a split A is not transposed")
+    m, n = tile + 8, tile + 24
+    a_bits, b_bits = inputs.gemm_operands(m, n, k, seed=tile + k, ta=ta, tb=tb)
+    lda, ldb, ldc = a_bits.shape[1] + 8, b_bits.shape[1] + 16, n + 8
+    a, b = _padded(a_bits, lda), _padded(b_bits, ldb)
+    ref = O.gemm(a_bits, b_bits, ta=ta, tb=tb)
+    if split:       # planes m * lda apart: the lo plane begins in the hi plane's last row of NaN
+        flat = torch.cat([a[:m].reshape(-1), (a.float() * 2.0 ** -8).to(torch.bfloat16).reshape(-1)])
+        a, ref = flat, ref * (1.0 + 2.0 ** -8)
+    bound = 2.0 ** -24 * k * (k / 4 + 1)
+    for dt in (torch.float32, torch.bfloat16):
+        c = nan_like((m + 1, ldc), dt)
+        _launch(B.gemm_op(a, b, c, m, n, k, ta=ta, tb=tb, tile=tile, a_split=split, lda=lda, ldb=ldb, ldc=ldc))
+        got = c[:m, :n]
+        assert torch.isnan(c[m].float()).all() and torch.isnan(c[:, n:].float()).all() and not torch.isnan(got.float()).any()
+        if dt is torch.float32:
+            assert np.abs(got.double().cpu().numpy() - ref).max() <= bound
+        else:
+            bf16_close(got, ref, abs_tol=bound)

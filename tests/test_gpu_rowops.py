@@ -317,3 +317,32 @@ def test_bias_of_odd_rows_stays_near_the_wide_form():
     y = torch.empty_like(x)
     t = [median_us(B.bias_act_op(x, y, rows, c, b, gelu=False)) for c in (1023, 1024)]
     assert t[0] <= 1.6 * t[1], t
+
+
+@pytest.mark.parametrize("rows,cols", [(9, 8), (6, 12), (5, 63), (4, 1023), (3, 1025), (2, 1032), (3, 4095), (2, 4096), (2, 4104)])
+@pytest.mark.parametrize("shift", [0, 2])
+def test_paired_bf16_outputs_in_every_variant(rows, cols, shift):
+    """hi + lo planes of the split and of LayerNorm's bf16 copy, for every access width and for planes that are only
+    4-byte aligned: hi is the rounded value, lo the rounded rest."""
+    x32 = inputs.normal_f32((rows, cols), [41, rows, cols], 2.0, 0.5)
+    g, b = inputs.normal_f32((cols,), 42, 0.02, 1.0), inputs.normal_f32((cols,), 43, 0.02)
+    x, gd, bd = torch.from_numpy(x32).cuda(), torch.from_numpy(g).cuda(), torch.from_numpy(b).cuda()
+    n = rows * cols
+    planes = lambda: nan_like((2 * n + 8,), torch.bfloat16)
+    buf = planes()
+    pair = buf[shift:shift + 2 * n].view(2, rows, cols)
+    launch(B.split_op(x, pair, rows, cols), atom_blocks=2)
+    assert torch.isnan(buf[:shift].float()).all() and torch.isnan(buf[shift + 2 * n:].float()).all()
+    assert torch.equal(pair[0], x.to(torch.bfloat16))
+    assert torch.equal(pair[1], (x - pair[0].float()).to(torch.bfloat16))
+    buf, y = planes(), nan_like((rows, cols), torch.float32)
+    pair = buf[shift:shift + 2 * n].view(2, rows, cols)
+    launch(B.layernorm_op(x, gd, bd, y, rows, cols, 1e-5, y_bf16=pair, split=True), atom_blocks=2)
+    assert torch.isnan(buf[:shift].float()).all() and torch.isnan(buf[shift + 2 * n:].float()).all()
+    ref = O.layernorm(x32.astype(np.float64), g.astype(np.float64), b.astype(np.float64), 1e-5)
+    f32_close(y, ref, 5e-5 * max(1.0, np.abs(ref).max()))
+    assert torch.equal(pair[0], y.to(torch.bfloat16))
+    assert torch.equal(pair[1], (y - pair[0].float()).to(torch.bfloat16))
+    single = nan_like((n + 8,), torch.bfloat16)[shift:shift + n].view(rows, cols)
+    launch(B.layernorm_op(x, gd, bd, y, rows, cols, 1e-5, y_bf16=single), atom_blocks=2)
+    assert torch.equal(single, pair[0])
