@@ -6,18 +6,18 @@
 
 namespace lithos {
 
-// ---- global -> register -> LDS staging of one [R x 64] operand tile ------
+// ---- global -> register -> LDS staging of one [256 x 64] operand tile ------
 // KSTRIDED = false: the operand is k-contiguous in memory (A[m][k], or B given
 // as [N,K]); a thread moves 16-byte chunks.
 // KSTRIDED = true: the operand is stored [k][row] (row-contiguous: A given as
 // [K,M], or B as [K,N]); a thread loads a KB x 8 block and writes it
 // transposed, so LDS always holds k-contiguous rows.
-template <int R, int T, bool KSTRIDED>
+constexpr int TILE = 256, TILE_T = 512;                         // output tile, threads (8 wavefronts, 2x4)
+
+template <bool KSTRIDED>
 struct TileStage {
-    static constexpr int NCH = R * 8 / T;                       // 16-byte registers per thread
-    static constexpr int KB = KSTRIDED ? (R >= T ? 8 : 8 * R / T) : 8;
-    static constexpr int NB = KSTRIDED ? (R >= T ? R / T : 1) : NCH;
-    static_assert(!KSTRIDED || KB >= 2, "tile too small for this workgroup size");
+    static constexpr int NCH = TILE * 8 / TILE_T;               // 16-byte registers per thread
+    static constexpr int KB = 4;                                // k-rows of a thread's block of a k-strided operand
     uint4 r[NCH];
 
     __device__ __forceinline__ void load(const uint16_t* base, int64_t ld, int row0, int rows_total,
@@ -26,7 +26,7 @@ struct TileStage {
         if constexpr (!KSTRIDED) {
 #pragma unroll
             for (int i = 0; i < NCH; ++i) {
-                int c = tid + i * T;
+                int c = tid + i * TILE_T;
                 int row = c >> 3, kc = c & 7;
                 int gr = min(row0 + row, rows_total - 1);
                 int k = k0 + kc * 8;
@@ -35,18 +35,14 @@ struct TileStage {
                 r[i] = v;
             }
         } else {
+            int nb = tid % (TILE / 8), kb = tid / (TILE / 8);
+            int gr = min(row0 + nb * 8, rows_total - 8);
 #pragma unroll
-            for (int i = 0; i < NB; ++i) {
-                int c = tid + i * T;
-                int nb = c % (R / 8), kb = c / (R / 8);
-                int gr = min(row0 + nb * 8, rows_total - 8);
-#pragma unroll
-                for (int q = 0; q < KB; ++q) {
-                    int k = k0 + kb * KB + q;
-                    uint4 v = make_uint4(0, 0, 0, 0);
-                    if (k < K) v = *reinterpret_cast<const uint4*>(base + (int64_t)k * ld + gr);
-                    r[i * KB + q] = v;
-                }
+            for (int q = 0; q < KB; ++q) {
+                int k = k0 + kb * KB + q;
+                uint4 v = make_uint4(0, 0, 0, 0);
+                if (k < K) v = *reinterpret_cast<const uint4*>(base + (int64_t)k * ld + gr);
+                r[q] = v;
             }
         }
     }
@@ -56,37 +52,27 @@ struct TileStage {
         if constexpr (!KSTRIDED) {
 #pragma unroll
             for (int i = 0; i < NCH; ++i) {
-                int c = tid + i * T;
+                int c = tid + i * TILE_T;
                 int row = c >> 3, kc = c & 7;
                 *reinterpret_cast<uint4*>(lds + lds_index(row, kc)) = r[i];
             }
         } else {
+            int nb = tid % (TILE / 8), kb = tid / (TILE / 8);
+            int kbase = kb * KB;
 #pragma unroll
-            for (int i = 0; i < NB; ++i) {
-                int c = tid + i * T;
-                int nb = c % (R / 8), kb = c / (R / 8);
-                int kbase = kb * KB;
+            for (int j = 0; j < 8; ++j) {               // j-th row of the 8-row block
+                int row = nb * 8 + j;
+                uint32_t w[KB / 2];
 #pragma unroll
-                for (int j = 0; j < 8; ++j) {           // j-th row of the 8-row block
-                    int row = nb * 8 + j;
-                    uint32_t w[KB / 2];
-#pragma unroll
-                    for (int p = 0; p < KB / 2; ++p) {  // pack k = 2p, 2p+1 of row j
-                        const uint4& lo4 = r[i * KB + 2 * p];
-                        const uint4& hi4 = r[i * KB + 2 * p + 1];
-                        uint32_t lo = (j < 2) ? lo4.x : (j < 4) ? lo4.y : (j < 6) ? lo4.z : lo4.w;
-                        uint32_t hi = (j < 2) ? hi4.x : (j < 4) ? hi4.y : (j < 6) ? hi4.z : hi4.w;
-                        if (j & 1) w[p] = (lo >> 16) | (hi & 0xffff0000u);
-                        else       w[p] = (lo & 0xffffu) | (hi << 16);
-                    }
-                    uint16_t* dst = lds + lds_index(row, kbase >> 3) + (kbase & 7);
-                    if constexpr (KB == 8)
-                        *reinterpret_cast<uint4*>(dst) = make_uint4(w[0], w[1], w[2], w[3]);
-                    else if constexpr (KB == 4)
-                        *reinterpret_cast<uint2*>(dst) = make_uint2(w[0], w[1]);
-                    else
-                        *reinterpret_cast<uint32_t*>(dst) = w[0];
+                for (int p = 0; p < KB / 2; ++p) {      // pack k = 2p, 2p+1 of row j
+                    const uint4& lo4 = r[2 * p];
+                    const uint4& hi4 = r[2 * p + 1];
+                    uint32_t lo = (j < 2) ? lo4.x : (j < 4) ? lo4.y : (j < 6) ? lo4.z : lo4.w;
+                    uint32_t hi = (j < 2) ? hi4.x : (j < 4) ? hi4.y : (j < 6) ? hi4.z : hi4.w;
+                    if (j & 1) w[p] = (lo >> 16) | (hi & 0xffff0000u);
+                    else       w[p] = (lo & 0xffffu) | (hi << 16);
                 }
+                *reinterpret_cast<uint2*>(lds + lds_index(row, kbase >> 3) + (kbase & 7)) = make_uint2(w[0], w[1]);
             }
         }
     }
@@ -96,11 +82,11 @@ struct TileStage {
 // Registers are capped so that a 256x256 tile keeps two wavefronts per SIMD (one 8-wave workgroup
 // per CU): left alone, the compiler spends the whole register file on hoisted epilogue addresses and halves the
 // occupancy.
-template <int BM, int BN, int WGM, int WGN, bool TA, bool TB, bool ST>
-__global__ __launch_bounds__(WGM * WGN * 64, 2)
+template <bool TA, bool TB, bool ST>
+__global__ __launch_bounds__(TILE_T, 2)
 void gemm_tile_kernel(GemmArgs g, AtomArgs atom)
 {
-    constexpr int T = WGM * WGN * 64, BK = 64;
+    constexpr int BM = TILE, BN = TILE, WGM = 2, WGN = 4, T = TILE_T, BK = 64;
     constexpr int WM = BM / WGM, WN = BN / WGN, MI = WM / 32, NI = WN / 32;
     // operand buffers; a staged epilogue needs room for the whole bf16 output tile
     constexpr int OPERAND_ELEMS = (BM + BN) * BK;
@@ -125,8 +111,8 @@ void gemm_tile_kernel(GemmArgs g, AtomArgs atom)
 #pragma unroll
             for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.0f;
 
-    TileStage<BM, T, TA> sa;        // A is k-strided in memory when transposed
-    TileStage<BN, T, !TB> sb;       // B is k-strided in memory when NOT transposed
+    TileStage<TA> sa;        // A is k-strided in memory when transposed
+    TileStage<!TB> sb;       // B is k-strided in memory when NOT transposed
 
     int kt0, kt1;
     slice_ktiles(g, blk.z, (g.K + BK - 1) / BK, kt0, kt1);
@@ -143,7 +129,7 @@ void gemm_tile_kernel(GemmArgs g, AtomArgs atom)
     for (int kt = kt0; kt < KT; ++kt) {
         if (kt + 1 < KT) {          // next tile's global loads fly during the MFMAs
             sa.load(g.A, g.lda, m0, g.M, (kt + 1) * BK, g.K, tid);
-                sb.load(g.B, g.ldb, n0, g.N, (kt + 1) * BK, g.K, tid);
+            sb.load(g.B, g.ldb, n0, g.N, (kt + 1) * BK, g.K, tid);
         }
 #pragma unroll
         for (int kk = 0; kk < BK / 16; ++kk) {
@@ -234,10 +220,8 @@ void gemm_tile_kernel(GemmArgs g, AtomArgs atom)
     });
 }
 
-#define LITHOS_TILE_PICK4(BMN, WGM, WGN, ST)                                                    \
-    (ta ? (tb ? (gemm_fn)gemm_tile_kernel<BMN, BMN, WGM, WGN, true, true, ST>                   \
-              : (gemm_fn)gemm_tile_kernel<BMN, BMN, WGM, WGN, true, false, ST>)                 \
-        : (tb ? (gemm_fn)gemm_tile_kernel<BMN, BMN, WGM, WGN, false, true, ST>                  \
-              : (gemm_fn)gemm_tile_kernel<BMN, BMN, WGM, WGN, false, false, ST>))
+#define LITHOS_TILE_PICK(ST)                                                                            \
+    (ta ? (tb ? (gemm_fn)gemm_tile_kernel<true, true, ST> : (gemm_fn)gemm_tile_kernel<true, false, ST>)   \
+        : (tb ? (gemm_fn)gemm_tile_kernel<false, true, ST> : (gemm_fn)gemm_tile_kernel<false, false, ST>))
 
 } // namespace lithos

@@ -3,6 +3,6 @@
 
 namespace lithos {
 
-gemm_fn gemm_tile256_elem_fn(bool ta, bool tb) { return LITHOS_TILE_PICK4(256, 2, 4, false); }
+gemm_fn gemm_tile256_elem_fn(bool ta, bool tb) { return LITHOS_TILE_PICK(false); }
 
 } // namespace lithos

@@ -3,6 +3,6 @@
 
 namespace lithos {
 
-gemm_fn gemm_tile256_wide_fn(bool ta, bool tb) { return LITHOS_TILE_PICK4(256, 2, 4, true); }
+gemm_fn gemm_tile256_wide_fn(bool ta, bool tb) { return LITHOS_TILE_PICK(true); }
 
 } // namespace lithos
