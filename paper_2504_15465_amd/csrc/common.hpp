@@ -82,18 +82,21 @@ __device__ __forceinline__ uint16_t f32_to_bf16(float f) { return (uint16_t)pack
 
 __device__ __forceinline__ float bf16_to_f32(uint16_t h) { return __uint_as_float((uint32_t)h << 16); }
 
-// GELU u * Phi(u).  |u| < 1.25: Phi = 1/2 + u P(u^2), 1.2e-8 of Phi(-|u|) at worst.  Beyond: Phi(-|u|) = exp(-u^2 / 2) t Q(t)
-// with t = 1 / (1 + |u| / 4), 8e-9 relative up to |u| = 14, where the exponential leaves the normal numbers; the upper
-// half is 1 minus that.  (Both fitted by iteratively reweighted least squares in float64, the coefficients rounded one
-// after the other.)  Neither half serves alone: near 0 the second would be 1 minus a number near 1/2 that carries the
-// roundings of the reciprocal, the polynomial and the exponential, and 1 + erff cancels for u < -1.
+// GELU u * Phi(u).  |u| < 1.25: Phi = 1/2 + u P(u^2), 1.2e-8 of Phi(-|u|) at worst.  Beyond: max(u, 0) - |u| Phi(-|u|), where
+// |u| Phi(-|u|) = exp(-u^2 / 2) R(t) with t = 1 / (1 + 0.3 |u|), 2.3e-8 relative up to |u| = 14, where the exponential leaves
+// the normal numbers.  (Both fitted by iteratively reweighted least squares in float64, the coefficients rounded one after
+// the other.)  Neither half serves alone: near 0 the second would subtract a number near u / 2 that carries the roundings
+// of the reciprocal, the polynomial and the exponential, and 1 + erff cancels for u < -1.
 // Measured on 4M uniform points a range against float64, worst / mean relative error (0.5 u (1 + erff) in brackets):
-//   -5 .. -2    1.5e-6 / 2.2e-7  (4.8e-2 / 1.7e-3)     0 .. 0.5    1.2e-7 / 3.2e-8  (1.3e-7 / 3.3e-8)
-//   -2 .. -1    5.2e-7 / 8.9e-8  (1.2e-6 / 1.7e-7)     0.5 .. 2    1.2e-7 / 2.6e-8  (1.4e-7 / 3.0e-8)
-//   -1 .. -0.5  2.0e-7 / 4.0e-8  (2.7e-7 / 5.6e-8)     2 .. 4      9.7e-8 / 2.4e-8  (1.1e-7 / 2.7e-8)
-//   -0.5 .. 0   1.3e-7 / 2.9e-8  (1.5e-7 / 3.1e-8)     4 .. 14     8.8e-8 / 4.7e-9  (1.0e-7 / 5.0e-9)
-// and 3.8e-7 absolute at worst, for u in [4, 8) (4.5e-7).  26 instructions and two transcendentals without a branch; erff runs
-// both of its branches in nearly every wavefront.  bias + GELU of 16384 x 1024 bf16: 20.7 us against 38.7.
+//   -5 .. -2    1.4e-6 / 2.1e-7  (4.8e-2 / 1.7e-3)     0 .. 0.5    1.2e-7 / 3.2e-8  (1.3e-7 / 3.3e-8)
+//   -2 .. -1    3.7e-7 / 7.1e-8  (1.2e-6 / 1.7e-7)     0.5 .. 2    1.1e-7 / 2.4e-8  (1.4e-7 / 3.0e-8)
+//   -1 .. -0.5  2.0e-7 / 4.0e-8  (2.7e-7 / 5.6e-8)     2 .. 4      6.5e-8 / 2.0e-8  (1.1e-7 / 2.7e-8)
+//   -0.5 .. 0   1.3e-7 / 2.9e-8  (1.5e-7 / 3.1e-8)     4 .. 14     6.0e-8 / 4.3e-9  (1.0e-7 / 5.0e-9)
+// and 2.4e-7 absolute at worst, for u in [4, 8) (4.5e-7).  22 instructions and two transcendentals; erff runs both of its
+// branches in nearly every wavefront.  BRANCH: the last step under a condition instead of both results and a select, the
+// same bits: bias + GELU of 16384 x 1024 bf16 20.0 us against 21.6 (erff: 38.7), but the 1003 x 3000 x 1160 GEMM's epilogue
+// makes 28.4 of 26.5 us.
+template <bool BRANCH = false>
 __device__ __forceinline__ float gelu_erf(float u)
 {
     const float z = u * u;
@@ -103,19 +106,23 @@ __device__ __forceinline__ float gelu_erf(float u)
     p = fmaf(p, z, 0.009970515966415405f);
     p = fmaf(p, z, -0.06648968905210495f);
     p = fmaf(p, z, 0.398942232131958f);
-    const float t = __builtin_amdgcn_rcpf(fmaf(fabsf(u), 0.25f, 1.0f));
-    float q = -0.04812637344002724f;
-    q = fmaf(q, t, 0.11394011229276657f);
-    q = fmaf(q, t, -0.029026754200458527f);
-    q = fmaf(q, t, 0.09738033264875412f);
-    q = fmaf(q, t, 0.07127942889928818f);
-    q = fmaf(q, t, 0.0951959639787674f);
-    q = fmaf(q, t, 0.099573515355587f);
-    q = fmaf(q, t, 0.099742092192173f);
-    q *= t;
+    const float t = __builtin_amdgcn_rcpf(fmaf(fabsf(u), 0.3f, 1.0f));
+    float r = 0.1794036477804184f;
+    r = fmaf(r, t, -0.43955719470977783f);
+    r = fmaf(r, t, 0.15026725828647614f);
+    r = fmaf(r, t, -0.2037215232849121f);
+    r = fmaf(r, t, -0.04562024399638176f);
+    r = fmaf(r, t, -0.039673078805208206f);
+    r = fmaf(r, t, 0.0002813413448166102f);
+    r = fmaf(r, t, 0.39893439412117004f);
     const float e = __builtin_amdgcn_exp2f(z * -0.72134752044448170368f);
-    const float tail = fmaf(e, u >= 0.0f ? -q : q, u >= 0.0f ? 1.0f : 0.0f);
-    return u * (fabsf(u) < 1.25f ? fmaf(u, p, 0.5f) : tail);
+    const float relu = fmaf(0.5f, fabsf(u), 0.5f * u);          // NaN at -infinity, as 0.5 u (1 + erff)
+    if constexpr (BRANCH) {
+        if (fabsf(u) < 1.25f) return u * fmaf(u, p, 0.5f);
+        return fmaf(-e, r, relu);
+    }
+    const float near = u * fmaf(u, p, 0.5f), far = fmaf(-e, r, relu);
+    return fabsf(u) < 1.25f ? near : far;
 }
 
 inline bool aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15u) == 0; }

@@ -133,7 +133,7 @@ __device__ __forceinline__ void drop_rounded(float (&v)[W])
 // accesses, one column index per thread.  W = 1: any sizes; a thread's elements are 256 apart and its column
 // index is stepped, not divided for.  All loads of x come first and unconditionally (beyond the tensor: its last elements,
 // which nobody stores): the compiler waits for a conditional load where it is issued.  Bound by HBM once neither a
-// 64-bit remainder per element nor erff is in the way: 16384 x 1024 bf16 13.8 us without and 20.7 with GELU (33 and 38.7),
+// 64-bit remainder per element nor erff is in the way: 16384 x 1024 bf16 13.8 us without and 20.0 with GELU (33 and 38.7),
 // 16384 x 1023 18.0 and 25 (33 and 38; 25 and 31 with conditional loads), fp32 without GELU 26.4 (27.1; 28.0).
 template <bool IN32, bool OUT32, int W>
 __global__ __launch_bounds__(256) void bias_act_kernel(RowArgs a, AtomArgs atom)
@@ -160,7 +160,7 @@ __global__ __launch_bounds__(256) void bias_act_kernel(RowArgs a, AtomArgs atom)
         }
         if (a.flags & LITHOS_F_GELU)
 #pragma unroll
-            for (int e = 0; e < W; ++e) v[i][e] = gelu_erf(v[i][e]);
+            for (int e = 0; e < W; ++e) v[i][e] = gelu_erf<true>(v[i][e]);
         store_run<OUT32>(a.y, idx, v[i]);
         if (!OUT32 && (a.flags & LITHOS_F_OUT_SPLIT)) {      // lo plane follows the hi plane
             drop_rounded(v[i]);
