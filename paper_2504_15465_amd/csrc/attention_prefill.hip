@@ -14,11 +14,12 @@
 //                 transposing LDS load (ds_read_b64_tr_b16), so nothing is transposed by hand.
 // The key and value blocks go from global memory straight into one of two LDS stages
 // (global_load_lds_dwordx4) a block ahead, with one barrier per block; all four wavefronts read them.  8192 tokens, 32/8
-// heads: 575 us, 956 TFLOP/s (through registers and one stage, two barriers per block: 643).  Raising the priority of the wavefronts
-// in their MFMAs (s_setprio) costs 3 to 5 % with two stages, on 256 and on 64 CUs alike, and the
-// high-priority neighbours of this best-effort kernel wait longer: p99 of an MLP request beside 16384 tokens 699 us
-// against 675.  Probabilities are rounded to bf16 for the second
-// product; the normalisation is applied to the fp32 result.
+// heads: 575 us, 956 TFLOP/s (through registers and one stage, two barriers per block: 643).  MFMA pipes 44 % busy, LDS
+// 23 %, 8.0 vector instructions per MFMA, a quarter of the wavefronts' time in waits: the softmax's arithmetic, the LDS
+// reads and the MFMAs of the two wavefronts of a SIMD overlap only by chance.  Raising the priority of the wavefronts in
+// their MFMAs (s_setprio) costs 3 to 5 % with two stages, on 256 and on 64 CUs alike, and the high-priority neighbours
+// of this best-effort kernel wait longer: p99 of an MLP request beside 16384 tokens 699 us against 675.  Probabilities
+// are rounded to bf16 for the second product; the normalisation is applied to the fp32 result.
 //
 // The tile a workgroup computes is named by its LOGICAL block index (LithOS Section 4.4), so
 // any sub-range of blocks is a valid atom, and every block does the same amount of work.

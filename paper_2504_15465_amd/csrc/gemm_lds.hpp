@@ -38,11 +38,12 @@ constexpr int wait_imm(int n) { return (n & 15) | 0x70 | ((n >> 4) << 14); }
 // wavefront and instruction) S - 1 tiles ahead, with one barrier per tile; operand fragments of step kk + 1 are
 // read before the MFMAs of step kk, across the barrier too.  A chunk beyond K is fetched from gemm_zero_chunk.
 //
-// Bound by latency: the MFMA pipes are 36-45 % busy and the LDS a fifth on the encoder's shapes.  Against the form
-// that staged through registers into one buffer: 1003 x 3000 x 1160 with epilogue 55 -> 26 us, split 4096 x 3072 x 768
-// 61 us (630 TFLOP/s of its two products), encoder of 12 layers at 4096 tokens 3360 -> 2770 us, at 128 tokens on 64 CUs
-// 1583 -> 1160 us.  One 64-deep k-tile more in flight for the 128 tile (144 KB of LDS, one workgroup per CU) is 12 %
-// faster with 192 tiles on 256 CUs and 2-20 % slower with more tiles per CU, so two workgroups per CU it is.
+// Bound by latency: on the encoder's shapes the MFMA pipes are busy 36 % (768 tiles, split A), 28 % (192 tiles, K = 3072) and
+// 23 % (768 tiles, plain) of the cycles, the LDS 11 to 16 %.  Against the form that staged through registers into one
+// buffer: 1003 x 3000 x 1160 with epilogue 59 -> 26.5 us, split 4096 x 3072 x 768 62 us (620 TFLOP/s of its two
+// products), encoder of 12 layers at 4096 tokens 3645 -> 2768 us, at 128 tokens on 64 CUs 1669 -> 1164 us.  One 64-deep
+// k-tile more in flight for the 128 tile (144 KB of LDS, one workgroup per CU) is 12 % faster with 192 tiles on 256 CUs
+// and 2-20 % slower with more tiles per CU, so two workgroups per CU it is.
 template <int BM, int BN, int WGM, int WGN, int KG, int BK, int S, int MINW, bool TA, bool TB, bool SPLIT, bool ST>
 __global__ __launch_bounds__(WGM * WGN * KG * 64, MINW)
 void gemm_lds_kernel(GemmArgs g, AtomArgs atom)
