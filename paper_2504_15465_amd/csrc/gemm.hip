@@ -128,7 +128,9 @@ int gemm_plan(const lithos_op_t& op, OpPlan* plan)
         // time (us, two groups / one: 1024 x 1024 x 8192 NN 47 / 65, split 128 x 768 x 3072 19 / 22).  More blocks hide it,
         // and the second group only waits in the prologue and epilogue (8192 x 1024 x 512 NT 25 / 21, 4096 x 4096 x 64
         // 29 / 17, 4096^3 NN 240 / 211, split 4096 x 768 x 3072 59 / 52), up to chains so long that more blocks in
-        // flight cost more in L2 than they hide (8192^3 TN 1661 / 2204, NN 1711 / 1708).
+        // flight cost more in L2 than they hide (8192^3 TN 1661 / 2204, NN 1711 / 1708).  Such a grid cut into atoms far
+        // smaller than what the chip holds would still run faster with two groups (2048^3 in atoms of 64 blocks 183 / 234,
+        // of 512 36 / 41); atoms are whole waves of resident workgroups.
         const uint64_t blocks = (uint64_t)plan->grid.x * plan->grid.y * plan->grid.z;
         if (tile == 64 && (blocks <= 512 || (!split && K / plan->grid.z > 4096))) variant = V_TILE64_2K;
     } else {

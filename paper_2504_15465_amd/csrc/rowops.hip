@@ -273,7 +273,7 @@ __global__ __launch_bounds__(256) void layernorm_kernel(RowArgs a, AtomArgs atom
 // Register-resident variant: the row is read ONCE and stays in registers (16 elements per thread) for the
 // mean, the centred variance and the output; needs H <= 16 * TPR and rows that 16-byte accesses fit: a thread holds
 // 16 / W runs of W = 4 (fp32) or 8 (bf16) consecutive elements.  Bound by HBM on many rows (16384 x 1024 bf16: 16.3 us
-// = 4.1 TB/s), by launch and latency on few.  Other rows take the general kernel above: with single elements this form
+// by events = 4.1 TB/s, 14.0 in a kernel trace), by launch and latency on few.  Other rows take the general kernel above: with single elements this form
 // has 16 conditional loads of x, gamma and beta each in a row, and the compiler waits for every one where it is issued
 // (16384 x 1025 bf16: 151 us against 46, 16384 x 127: 25 against 10).
 template <bool IN32, bool OUT32, int TPR, int W>

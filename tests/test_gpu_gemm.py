@@ -735,20 +735,20 @@ def test_epilogue_of_ragged_tiles_costs_little():
     assert t[0] <= 1.9 * t[1], t
 
 
-@pytest.mark.parametrize("split", [False, True])
-@pytest.mark.parametrize("ta,tb,m,n,k,slices", [
+GROUP_SHAPES = [
     (False, False, 1024, 2048, 72, 0),      # 512 blocks: two groups of wavefronts
     (False, True, 1025, 2051, 136, 0),      # 561 blocks, ragged everywhere: one group
     (False, False, 1480, 1480, 8, 0),       # 576 blocks, one k-tile of 8
+    (False, True, 1470, 1480, 4168, 0),     # 552 blocks with a long chain: two groups (one with a split A)
     (True, False, 512, 584, 1000, 8),       # 640 blocks in 8 K slices
     (True, True, 1480, 1485, 64, 0),
-    (False, True, 1470, 1480, 4168, 0),     # 552 blocks with a long chain: two groups (one with a split A)
-])
+]
+
+
+@pytest.mark.parametrize("ta,tb,m,n,k,slices,split", [s + (False,) for s in GROUP_SHAPES] + [s + (True,) for s in GROUP_SHAPES[:4]])
 def test_64_tile_with_one_and_two_groups_of_wavefronts(ta, tb, m, n, k, slices, split):
     """Both sides of the rule by the number of blocks, in every layout: against the oracle, and the same bits however the
     launch is cut.  fp32 sums: at most K * 2^-24 of the sum of magnitudes (K / 4 for uniform operands)."""
-    if split and (ta or slices):
-        pytest.skip("a split A is not transposed; slices as without")
     a_bits, b_bits = inputs.gemm_operands(m, n, k, seed=k + m, ta=ta, tb=tb)
     a, b = dev_bits(a_bits), dev_bits(b_bits)
     ref = O.gemm(a_bits, b_bits, ta=ta, tb=tb)
@@ -785,15 +785,14 @@ def _padded(bits, cols):
     return t
 
 
-@pytest.mark.parametrize("tile,split", [(64, False), (64, True), (128, False), (128, True)])
-@pytest.mark.parametrize("ta,tb", [(False, False), (False, True), (True, False), (True, True)])
+@pytest.mark.parametrize("tile", [64, 128])
+@pytest.mark.parametrize("ta,tb,split", [(False, False, False), (False, True, False), (True, False, False), (True, True, False),
+                                         (False, False, True), (False, True, True)])
 @pytest.mark.parametrize("k", [8, 72, 200])
 def test_padding_between_rows_is_never_used(tile, split, ta, tb, k):
     """Operands and C inside larger buffers: NaN behind every row of A and B and in the row below reaches no result
     (tiles read past K and past the last row from elsewhere), and the padding of C stays as it was.
     fp32 sums: at most K * 2^-24 of the sum of magnitudes (K / 4 for uniform operands)."""
-    if split and ta:
-        pytest.skip("a split A is not transposed")
     m, n = tile + 8, tile + 24
     a_bits, b_bits = inputs.gemm_operands(m, n, k, seed=tile + k, ta=ta, tb=tb)
     lda, ldb, ldc = a_bits.shape[1] + 8, b_bits.shape[1] + 16, n + 8
