@@ -2,7 +2,7 @@
 // This file validates a GEMM descriptor, picks the kernel and launches one atom.
 //
 // Kernel families (one translation unit each):
-//  * gemm_lds256_kernel (gemm_lds256.hpp, gemm_lds256_{wide,elem}.hip) - 256x256 tiles, K % 64 == 0, any operand
+//  * gemm_lds256_kernel (gemm_lds256.hpp, gemm_lds256{,_ta}.hip) - 256x256 tiles, K % 64 == 0, any operand
 //    layout: global memory straight into LDS, k-strided operands read with the
 //    transposing LDS load; the best-effort and training-shaped GEMMs;
 //  * gemm_lds_kernel (gemm_lds.hpp, gemm_tile{64,128}.hip) - 64 and 128 tiles, any K % 8 == 0, split-bf16 A;
@@ -26,7 +26,9 @@ namespace lithos {
 
 // ---- host side -------------------------------------------------------------
 
-static int tile_threads(int variant) { return variant == V_TILE64 || variant == V_TILE128 ? 256 : 512; }
+constexpr int64_t LDS256_MAX_LD = 1 << 22;      // elements: 256 rows are 2 GiB
+
+static int tile_threads(int variant) { return variant == V_TILE64 || variant == V_TILE128 || variant == V_LDS256 ? 256 : 512; }
 
 // full bf16 tiles can leave through LDS when whole 16-byte pieces of C rows are addressable
 // (fp32 tiles of the same kernels are stored from registers, 16 bytes per lane)
@@ -42,7 +44,7 @@ static int norm_of(uint32_t flags) { return (flags & LITHOS_F_NORM_LN) ? 1 : (fl
 static gemm_fn variant_fn(int variant, bool ta, bool tb, bool a32, bool split, bool st, int norm)
 {
     switch (variant) {
-    case V_LDS256: return st ? gemm_lds256_wide_fn(ta, tb) : gemm_lds256_elem_fn(ta, tb);
+    case V_LDS256: return ta ? gemm_lds256_ta_fn(tb) : gemm_lds256_fn(tb);
     case V_TILE64: return gemm_tile64_fn(ta, tb, split, st, false);
     case V_TILE64_2K: return gemm_tile64_fn(ta, tb, split, st, true);
     case V_TILE128: return gemm_tile128_fn(ta, tb, split, st);
@@ -121,7 +123,8 @@ int gemm_plan(const lithos_op_t& op, OpPlan* plan)
         if (fused) return fail(LITHOS_EINVAL, "gemm: NORM_LN, NORM_RMS and GLU are built into the weight-streaming kernel only (TRANS_B, M <= 16)");
         if (split && tile == 256) return fail(LITHOS_EINVAL, "gemm: SPLIT_A is built for the 64 and 128 tiles only");
         variant = tile == 64 ? V_TILE64 : tile == 128 ? V_TILE128 : V_TILE256;
-        if (tile == 256 && K % 64 == 0) variant = V_LDS256;
+        // the kernel's 32-bit byte offsets reach 256 rows of this length
+        if (tile == 256 && K % 64 == 0 && lda <= LDS256_MAX_LD && ldb <= LDS256_MAX_LD) variant = V_LDS256;
         plan->grid = {(uint32_t)((N + tile - 1) / tile), (uint32_t)((M + tile - 1) / tile), (uint32_t)(slices > 1 ? slices : 1)};
         // The 64 tile splits K between two groups of wavefronts while all blocks of the whole grid (never of an atom: the
         // sums must not depend on the cut) find room at two per CU of the whole chip: then the chain of k-tiles is the
@@ -158,6 +161,7 @@ int gemm_launch(const lithos_op_t& op, const OpPlan& plan, const AtomArgs& atom,
     g.a_plane = op.dim[3]; g.c_plane = op.dim[4];
     g.k_slices = (int)op.dim[5]; g.c_slice = op.dim[6];
     g.gamma = (const float*)op.in[4]; g.colsum = (const float*)op.in[5]; g.ldcs = op.dim[7]; g.eps = op.fparam[0];
+    g.wide = staged_epilogue(op);
     gemm_fn fn = variant_fn(plan.variant, op.flags & LITHOS_F_TRANS_A, op.flags & LITHOS_F_TRANS_B, op.flags & LITHOS_F_IN_F32,
                             op.flags & LITHOS_F_SPLIT_A, staged_epilogue(op), norm_of(op.flags));
     LITHOS_HIP(launch_kernel(fn, dim3(LITHOS_ATOM_LAUNCH_BLOCKS(atom)), dim3(plan.threads), s, g, atom));

@@ -31,6 +31,7 @@ struct GemmArgs {
     const float* colsum; // NORM_LN: [2, ldcs] = the rows gamma and beta multiplied with op(B)
     int64_t ldcs;
     float eps;
+    int wide;            // whole 16-byte pieces of C can be stored (see staged_epilogue)
 };
 
 // K slices (the logical grid's z axis): slice z of S owns the k-tiles [z*KT/S, (z+1)*KT/S),
@@ -112,6 +113,15 @@ __device__ __forceinline__ void epilogue_store_block(const GemmArgs& g, int m, i
             if (row(e) < g.M && col(e) < g.N) store_value(g, first + (8 * (e >> 2) + (e & 3)) * step, v[e]);
         });
     }
+}
+
+__device__ __forceinline__ void wave_lds_sync()
+{
+    // LDS operations of one wavefront complete in order; this only stops the compiler
+    // from moving reads of other lanes' data across the writes
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
 // ---- epilogue of a full bf16 tile through LDS ---------------------------------
@@ -239,8 +249,8 @@ gemm_fn gemm_tile64_fn(bool ta, bool tb, bool split, bool st, bool two_groups);
 gemm_fn gemm_tile128_fn(bool ta, bool tb, bool split, bool st);
 gemm_fn gemm_tile256_wide_fn(bool ta, bool tb);
 gemm_fn gemm_tile256_elem_fn(bool ta, bool tb);
-gemm_fn gemm_lds256_wide_fn(bool ta, bool tb);
-gemm_fn gemm_lds256_elem_fn(bool ta, bool tb);
+gemm_fn gemm_lds256_fn(bool tb);
+gemm_fn gemm_lds256_ta_fn(bool tb);
 gemm_fn gemm_skinny_fn(int variant, bool a32, int norm);
 
 constexpr int SKINNY_WAVES = 8;     // wavefronts per workgroup of the skinny kernels, each owning one slice of K

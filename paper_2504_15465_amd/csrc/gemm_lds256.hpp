@@ -3,217 +3,277 @@
 
 namespace lithos {
 
-// ---- 256x256 tile, K a multiple of 64, global -> LDS without registers -------------
-// The k-tiles go from global memory straight into LDS (global_load_lds_dwordx4: the 64
-// lanes of a wavefront fill 1 KB of LDS in lane order, so each lane fetches the 16-byte
-// chunk that the swizzled layout wants at its position).  That frees the 32 staging
-// registers of the general kernel, which pay for a second set of operand fragments:
-// the LDS reads of step kk+1 are issued before the MFMAs of step kk.
+// ---- 256x256 tile, K a multiple of 64, any operand layout ---------------------------
+// Four wavefronts of 128x128, one per SIMD: 256 accumulator registers and 256 for the rest.
 //
-// An operand that is k-contiguous in memory (A [M,K]; B given as [N,K]) lies in LDS as
-// [row][64 k] and a lane reads its 8 consecutive k with one 16-byte load.  An operand that
-// is k-strided in memory (KSA: A given as [K,M]; KSB: B given as [K,N]) lies in LDS as it
-// lies in memory, [64 k][256 rows], and is read with the transposing LDS load
-// (ds_read_b64_tr_b16): within 16 lanes, source lane s supplies 4 consecutive rows of
-// k-row s/4, and lane l receives row l of the four k-rows: 4 consecutive k of one row,
-// which is the MFMA operand layout.  Two such loads make a fragment; nothing is
-// transposed in registers.
+// What bounds it: on random data the chip lowers its clock with the power that the MFMAs and everything around them
+// take (8192^3: 2.39 GHz on zeros, 1.55 to 1.9 on random data, the more the busier the MFMA pipes), so a kernel that
+// only fills the pipes better gains little, and one that does less beside the MFMAs gains twice.  Hence
+//  * 128x128 per wavefront: 8 + 8 KB of LDS reads for 64 MFMAs; 128x64 reads half as much again;
+//  * v_mfma_f32_16x16x32_bf16: per multiplication it moves half the accumulators of the 32x32x16 form, and twice the
+//    operands, 0.5 bytes against 0.625: 8192^3 NN 735 us against 773;
+//  * no vector instruction in the loop but MFMAs and LDS reads: the k-tiles come by buffer_load ... lds, whose base
+//    advances in scalar registers and whose range is set to nothing behind the last tile (zeros arrive, no memory
+//    is read); addresses in vector registers and a select per load made 820 of the 773;
+//  * each MFMA is followed by at most one LDS read or load, in this order, so that the pipe never waits for the issue.
+// The accumulators are named as AGPRs in inline assembly: left to itself the register allocator moves them
+// between the two halves of the register file in every k-tile (8192^3: 5644 us).
+//
+// k-tiles are 32 deep in four LDS stages of 32 KB: during tile t the fragments of tile t + 1 are read into the second
+// register set and tile t + 4 is fetched into the stage of tile t, whose fragments were read a tile before; one barrier
+// per tile.  64-deep tiles in two stages (one tile ahead) take 929 us: the first touch of a k range comes from beyond L2.
+//
+// An operand that is k-contiguous in memory (A [M,K]; B given as [N,K]) lies in LDS as lines of 128 bytes, two rows
+// of 32 k each, and a lane reads its 8 consecutive k with one 16-byte load.  An operand that is k-strided in
+// memory (KSA: A given as [K,M]; KSB: B given as [K,N]) lies in LDS as it lies in memory, [32 k][256 rows],
+// and is read with the transposing LDS load (ds_read_b64_tr_b16): within 16 lanes, source lane s supplies 4
+// consecutive rows of k-row s/4, and lane l receives row l of the four k-rows: 4 consecutive k of one row, which is
+// the MFMA operand layout.  Two such loads make a fragment; nothing is transposed in registers.
+//
+// 8192^3 NN 864 -> 735 us (1495 TFLOP/s; eight wavefronts of 128x64, 64-deep tiles, before), 4096^3 111 -> 96,
+// 16384 x 1024 x 4096 NT 121 -> 105, 16384 x 4096 x 1024 NN 131 -> 122.
 
-// [64 k][256 rows] tile: 16-byte chunk c of k-row k is stored at chunk c ^ ((k & 3) << 2), so
-// the four k-rows that one transposing load touches fall into different banks.
-__device__ __forceinline__ int ks_index(int k, int row) { return k * 256 + ((((row >> 3) ^ ((k & 3) << 2))) << 3) + (row & 7); }
+typedef float f32x4a __attribute__((ext_vector_type(4)));
 
-template <int WGM, int WGN, bool ST, bool KSA, bool KSB>
-__global__ __launch_bounds__(WGM * WGN * 64)
+// The compiler does not see the latency of an MFMA written here: the accumulators are first read by other
+// instructions behind the loop's last barrier and mfma16_settle.
+__device__ __forceinline__ void mfma16_agpr(f32x4a& c, bf16x8 x, bf16x8 y)
+{
+    asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+a"(c) : "v"(x), "v"(y));
+}
+// A block of accumulators in vector registers, from here on: copies of all 64 blocks ahead of the epilogue's first branch
+// would go to memory.
+__device__ __forceinline__ f32x4a agpr_read(f32x4a& c)
+{
+    asm volatile("" : "+a"(c));
+    return c;
+}
+__device__ __forceinline__ void mfma16_settle() { asm volatile("s_nop 15\n\ts_nop 15" ::: "memory"); }
+
+template <bool KSA, bool KSB>
+__global__ __launch_bounds__(256, 1)
 void gemm_lds256_kernel(GemmArgs g, AtomArgs atom)
 {
-    static_assert(!ST || (WGM == 2 && WGN == 4), "the staged epilogue maps 32-row blocks to the four 64-row buffers");
-    constexpr int BM = 256, BN = 256, BK = 64, WM = BM / WGM, WN = BN / WGN, MI = WM / 32, NI = WN / 32;
-    constexpr int NBLK = 32 / (WGM * WGN);          // 1 KB blocks of each operand that a wavefront fetches
-    // four separate arrays, each addressed statically: the compiler can then tell that the
-    // LDS reads of one stage do not depend on the loads in flight into the other
+#ifdef __HIP_DEVICE_COMPILE__       // the buffer types exist on the device only
+    constexpr int BM = 256, BN = 256, BK = 32, S = 4, MI = 8, NI = 8, NF = MI + NI, NM = MI * NI;
+    constexpr int NBLK = 4, NL = 2 * NBLK;          // 1 KB blocks of each operand that a wavefront fetches; loads per k-tile
+    // separate arrays, each addressed statically: the compiler can then tell that the LDS reads of one stage do
+    // not depend on the loads in flight into another
     __shared__ __attribute__((aligned(1024))) uint16_t A0[BM * BK];
     __shared__ __attribute__((aligned(1024))) uint16_t A1[BM * BK];
+    __shared__ __attribute__((aligned(1024))) uint16_t A2[BM * BK];
+    __shared__ __attribute__((aligned(1024))) uint16_t A3[BM * BK];
     __shared__ __attribute__((aligned(1024))) uint16_t B0[BN * BK];
     __shared__ __attribute__((aligned(1024))) uint16_t B1[BN * BK];
+    __shared__ __attribute__((aligned(1024))) uint16_t B2[BN * BK];
+    __shared__ __attribute__((aligned(1024))) uint16_t B3[BN * BK];
+    const auto stage_a = [&](auto s) __attribute__((always_inline)) -> uint16_t* {
+        constexpr int v = decltype(s)::value % S;
+        if constexpr (v == 0) return A0; else if constexpr (v == 1) return A1; else if constexpr (v == 2) return A2; else return A3;
+    };
+    const auto stage_b = [&](auto s) __attribute__((always_inline)) -> uint16_t* {
+        constexpr int v = decltype(s)::value % S;
+        if constexpr (v == 0) return B0; else if constexpr (v == 1) return B1; else if constexpr (v == 2) return B2; else return B3;
+    };
 
     const uint32_t L = atom_logical_block(atom);
     const Block3 blk = atom_delinearize(L, atom);
     uint32_t tm, tn;
     tile_of_block(blk.y * atom.gx + blk.x, g.tiles_m, g.tiles_n, tm, tn);   // blk.z is the K slice
-    const int m0 = tm * BM, n0 = tn * BN;
-    const int tid = threadIdx.x, lane = tid & 63;
+    const int m0 = __builtin_amdgcn_readfirstlane(tm) * BM, n0 = __builtin_amdgcn_readfirstlane(tn) * BN;
+    const uint32_t z = __builtin_amdgcn_readfirstlane(blk.z);
+    const int tid = threadIdx.x, lane = tid & 63, l16 = lane & 15, quad = lane >> 4;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int wm = wave / WGN, wn = wave % WGN;
+    const int wm = wave >> 1, wn = wave & 1;
+    int kt0, kt1;                                   // this block's k range in units of 64
+    slice_ktiles(g, z, g.K / 64, kt0, kt1);
+    const int n_it = __builtin_amdgcn_readfirstlane(kt1 - kt0) * 2;
+    const int64_t klo = __builtin_amdgcn_readfirstlane(kt0) * 64;
+    if (g.k_slices > 1) g.C = reinterpret_cast<float*>(g.C) + (int64_t)z * g.c_slice;
 
-    f32x16 acc[MI][NI];
+    // Wavefront w fills LDS blocks 4w .. 4w+3 of each operand's k-tile, lane l the 16-byte piece l of a block.
+    // k-contiguous: a block is 8 lines of two rows, piece p of line n holds chunk c of row 2n + r where 4r + c = p ^ (n & 7);
+    // rows beyond the matrix re-read its last row.  k-strided: a block is 2 k-rows of 32 chunks, piece p of k-row k holds
+    // chunk p ^ ((k & 3) << 2), so the four k-rows that one transposing load touches fall into different banks; chunks
+    // beyond the matrix re-read its last one.  Byte offsets from the tile's first row (gemm_plan bounds them).
+    const auto lane_off = [&](auto ks, int ld, int r0, int rows, int b) __attribute__((always_inline)) -> uint32_t {
+        if constexpr (decltype(ks)::value) {
+            const int k = b * 2 + (lane >> 5), c = (lane & 31) ^ ((k & 3) << 2);
+            return (uint32_t)(k * ld + min(c * 8, rows - 8 - r0)) * 2;
+        } else {
+            const int line = b * 8 + (lane >> 3), p = (lane & 7) ^ (line & 7);
+            return (uint32_t)(min(line * 2 + (p >> 2), rows - 1 - r0) * ld + (p & 3) * 8) * 2;
+        }
+    };
+    constexpr std::bool_constant<KSA> ksa{};
+    constexpr std::bool_constant<KSB> ksb{};
+    uint32_t oa[NBLK], ob[NBLK];
+#pragma unroll
+    for (int i = 0; i < NBLK; ++i) {
+        oa[i] = lane_off(ksa, (int)g.lda, m0, g.M, wave * NBLK + i);
+        ob[i] = lane_off(ksb, (int)g.ldb, n0, g.N, wave * NBLK + i);
+    }
+    const int64_t a_step = KSA ? g.lda * BK : BK, b_step = KSB ? g.ldb * BK : BK;
+    const uint16_t* pa = g.A + (KSA ? m0 + klo * g.lda : m0 * g.lda + klo);
+    const uint16_t* pb = g.B + (KSB ? n0 + klo * g.ldb : n0 * g.ldb + klo);
+    int to_fetch = n_it;
+    const auto load = [&](auto qc, uint16_t* At, uint16_t* Bt) __attribute__((always_inline)) {
+        constexpr int q = decltype(qc)::value;
+        const int range = __builtin_amdgcn_readfirstlane(~((to_fetch - 1) >> 31));      // everything, or nothing behind the last tile
+        if constexpr (q < NBLK)
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(__builtin_amdgcn_make_buffer_rsrc((void*)pb, 0, range, 0x00020000), (lptr_t)(Bt + (wave * NBLK + q) * 512), 16, ob[q], 0, 0, 0);
+        else
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(__builtin_amdgcn_make_buffer_rsrc((void*)pa, 0, range, 0x00020000), (lptr_t)(At + (wave * NBLK + q - NBLK) * 512), 16, oa[q - NBLK], 0, 0, 0);
+        if constexpr (q == NL - 1) { --to_fetch; pa += a_step; pb += b_step; }
+    };
+
+    // Where this lane reads in a stage.  A fragment is 16 rows: row l16, the 8 k of chunk `quad`.  k-contiguous: one
+    // offset for all of a wavefront's fragments.  k-strided: k-row 8 quad + l16/4, rows 4 (l16 % 4) .. +3 of the fragment's
+    // 16; the rotation mixes into bits 2 and 3 of the chunk, so fragments two apart need offsets of their own.
+    int ra[KSA ? 4 : 1], rb[KSB ? 4 : 1];
+    const auto read_base = [&](auto ks, int half, auto& r) __attribute__((always_inline)) {
+        if constexpr (decltype(ks)::value) {
+#pragma unroll
+            for (int v = 0; v < 4; ++v)
+                r[v] = (8 * quad + (l16 >> 2)) * 256 + half * 128 + ((v ^ (l16 >> 2)) << 5) + ((l16 & 3) >> 1) * 8 + (l16 & 1) * 4;
+        } else {
+            r[0] = half * 4096 + (l16 >> 1) * 64 + ((((l16 & 1) * 4 + quad) ^ (l16 >> 1)) << 3);
+        }
+    };
+    read_base(ksa, wm, ra);
+    read_base(ksb, wn, rb);
+    const auto frag = [&](auto ks, auto fc, const uint16_t* T, const auto& r) __attribute__((always_inline)) -> bf16x8 {
+        constexpr int f = decltype(fc)::value;
+        if constexpr (decltype(ks)::value) {
+            typedef __attribute__((address_space(3))) s16x4* tr_t;
+            const uint16_t* const p = T + r[f >> 1] + (f & 1) * 16;
+            const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((tr_t)p), hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((tr_t)(p + 4 * 256));
+            return __builtin_bit_cast(bf16x8, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
+        } else {
+            return __builtin_bit_cast(bf16x8, *reinterpret_cast<const uint4*>(T + r[0] + f * 512));
+        }
+    };
+
+    f32x4a acc[MI][NI];
 #pragma unroll
     for (int i = 0; i < MI; ++i)
 #pragma unroll
-        for (int j = 0; j < NI; ++j)
-#pragma unroll
-            for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.0f;
-
-    // Wavefront w fills LDS blocks 4w..4w+3 of each operand.  k-contiguous operand: a block is
-    // 8 rows x 8 chunks of 16 bytes, and lane l lands on row l/8, stored chunk l%8, which holds
-    // the logical chunk (l%8) ^ swizzle(row); rows beyond the matrix re-read its last row.
-    // k-strided operand: a block is 2 k-rows x 32 chunks, lane l lands on k-row l/32, stored
-    // chunk l%32; chunks beyond the matrix re-read the row's last chunk.
-    auto lane_ptr = [&](auto ks, const uint16_t* base, int64_t ld, int r0, int rows, int blkno) {
-        if constexpr (decltype(ks)::value) {
-            const int k = blkno * 2 + (lane >> 5);
-            const int c = (lane & 31) ^ ((k & 3) << 2);
-            return base + (int64_t)k * ld + min(r0 + c * 8, rows - 8);
-        } else {
-            const int row = blkno * 8 + (lane >> 3);
-            const int kc = (lane & 7) ^ ((row ^ (row >> 3)) & 7);
-            return base + (int64_t)min(r0 + row, rows - 1) * ld + kc * 8;
-        }
+        for (int j = 0; j < NI; ++j) acc[i][j] = f32x4a{0.f, 0.f, 0.f, 0.f};
+    bf16x8 fr[2][NF];                               // two sets of fragments, A's then B's, alternating between the tiles
+    // in the order of their first use: A's first, all of B's, the rest of A's
+    const auto read = [&](auto qc, const uint16_t* At, const uint16_t* Bt, auto set) __attribute__((always_inline)) {
+        constexpr int q = decltype(qc)::value;
+        if constexpr (q >= 1 && q <= NI) fr[decltype(set)::value][MI + q - 1] = frag(ksb, std::integral_constant<int, q - 1>{}, Bt, rb);
+        else { constexpr int a = q == 0 ? 0 : q - NI; fr[decltype(set)::value][a] = frag(ksa, std::integral_constant<int, a>{}, At, ra); }
     };
-    const uint16_t* ga[NBLK];
-    const uint16_t* gb[NBLK];
-#pragma unroll
-    for (int i = 0; i < NBLK; ++i) {
-        ga[i] = lane_ptr(std::bool_constant<KSA>{}, g.A, g.lda, m0, g.M, wave * NBLK + i);
-        gb[i] = lane_ptr(std::bool_constant<KSB>{}, g.B, g.ldb, n0, g.N, wave * NBLK + i);
+    const auto turn = [&](auto in_flight) __attribute__((always_inline)) {
+        // this wavefront's share of the tile that is read next has landed, its own LDS reads are done; then everybody's
+        __builtin_amdgcn_sched_barrier(0);
+        __builtin_amdgcn_s_waitcnt((decltype(in_flight)::value & 15) | 0x70 | ((decltype(in_flight)::value >> 4) << 14));
+        asm volatile("" ::: "memory");
+        __builtin_amdgcn_s_barrier();
+        asm volatile("" ::: "memory");
+        __builtin_amdgcn_sched_barrier(0);
+    };
+    constexpr int RS = NM * 3 / 4;                  // MFMAs that are followed by the reads of the next tile
+    const auto tile_step = [&](auto tc) __attribute__((always_inline)) {
+        constexpr int t = decltype(tc)::value;
+        constexpr std::integral_constant<int, t> cur{};
+        constexpr std::integral_constant<int, t + 1> next{};
+        turn(std::integral_constant<int, (S - 2) * NL>{});
+        static_for<NM>([&](auto mc) __attribute__((always_inline)) {
+            constexpr int m = decltype(mc)::value;
+            // operands exchanged: a lane then holds four consecutive columns of one row of C
+            mfma16_agpr(acc[m / NI][m % NI], fr[t & 1][MI + m % NI], fr[t & 1][m / NI]);
+            if constexpr (m < RS && (m + 1) * NF / RS > m * NF / RS)
+                read(std::integral_constant<int, m * NF / RS>{}, stage_a(next), stage_b(next), std::integral_constant<int, (t + 1) & 1>{});
+            if constexpr ((m + 1) * NL / NM > m * NL / NM)
+                load(std::integral_constant<int, m * NL / NM>{}, stage_a(cur), stage_b(cur));
+            __builtin_amdgcn_sched_barrier(0);
+        });
+    };
+
+    static_for<S>([&](auto s) __attribute__((always_inline)) { static_for<NL>([&](auto q) __attribute__((always_inline)) { load(q, stage_a(s), stage_b(s)); }); });
+    turn(std::integral_constant<int, (S - 1) * NL>{});
+    static_for<NF>([&](auto q) __attribute__((always_inline)) { read(q, A0, B0, std::integral_constant<int, 0>{}); });
+    // whole rounds of the stages, then the rest
+    int it = 0;
+    for (; it + S <= n_it; it += S) static_for<S>([&](auto t) __attribute__((always_inline)) { tile_step(t); });
+    if (it < n_it) {                                // n_it is even
+        tile_step(std::integral_constant<int, 0>{});
+        tile_step(std::integral_constant<int, 1>{});
     }
-    const int64_t a_kstep = KSA ? g.lda : 1, b_kstep = KSB ? g.ldb : 1;    // elements per unit of k
-    auto fetch = [&](uint16_t* Ad, uint16_t* Bd, int k0) {
-#pragma unroll
-        for (int i = 0; i < NBLK; ++i) {
-            __builtin_amdgcn_global_load_lds((gptr_t)(ga[i] + k0 * a_kstep), (lptr_t)(Ad + (wave * NBLK + i) * 512), 16, 0, 0);
-            __builtin_amdgcn_global_load_lds((gptr_t)(gb[i] + k0 * b_kstep), (lptr_t)(Bd + (wave * NBLK + i) * 512), 16, 0, 0);
-        }
-    };
+    turn(std::integral_constant<int, 0>{});         // the stages are free
+    mfma16_settle();
 
-    int kt0, KT;                                    // this block's k-tiles are [kt0, KT)
-    slice_ktiles(g, blk.z, g.K / BK, kt0, KT);
-    if (g.k_slices > 1) g.C = reinterpret_cast<float*>(g.C) + (int64_t)blk.z * g.c_slice;
-    // Operand fragments: set 0 and set 1 alternate between the four 16-wide k-steps of a tile.
-    bf16x8 af[2][MI], bfr[2][NI];
-    // one 32-row fragment of k-step kk: rows r0 .. r0+31 of the tile, this lane's 8 k
-    auto read_frag = [&](auto ks, const uint16_t* T, int r0, int kk) -> bf16x8 {
-        if constexpr (decltype(ks)::value) {
-            // source lane s of a 16-lane group addresses k-row s/4, rows 4*(s%4)..+3 of the group's 16
-            const int grp = lane >> 4, s = lane & 15;
-            const int k = kk * 16 + 8 * (grp >> 1) + (s >> 2);
-            const int row = r0 + 16 * (grp & 1) + 4 * (s & 3);
-            const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4*)(T + ks_index(k, row)));
-            const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4*)(T + ks_index(k + 4, row)));
-            return __builtin_bit_cast(bf16x8, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
-        } else {
-            return __builtin_bit_cast(bf16x8, *reinterpret_cast<const uint4*>(T + lds_index(r0 + (lane & 31), kk * 2 + (lane >> 5))));
-        }
-    };
-    auto read_frags = [&](const uint16_t* Ac, const uint16_t* Bc, int kk, bf16x8 (&a)[MI], bf16x8 (&b)[NI]) {
+    // lane: row l16 of a 16x16 block, columns 4 quad .. +3
+    const int mw = m0 + wm * 128, nw = n0 + wn * 128;
+    if (!g.wide || ((g.N & 7) && n0 + BN > g.N)) {  // element by element
+        static_for<MI * NI>([&](auto ij) __attribute__((always_inline)) {
+            constexpr int i = decltype(ij)::value / NI, j = decltype(ij)::value % NI;
+            const f32x4a v = agpr_read(acc[i][j]);
 #pragma unroll
-        for (int i = 0; i < MI; ++i) a[i] = read_frag(std::bool_constant<KSA>{}, Ac, wm * WM + i * 32, kk);
-#pragma unroll
-        for (int j = 0; j < NI; ++j) b[j] = read_frag(std::bool_constant<KSB>{}, Bc, wn * WN + j * 32, kk);
-    };
-    // the MFMAs of one step; the LDS reads of the next step are issued after the first NI of
-    // them, so that the wait in front of a step only covers reads that are a step old
-    auto mfmas = [&](const bf16x8 (&a)[MI], const bf16x8 (&b)[NI], int i0, int i1) {
-#pragma unroll
-        for (int i = i0; i < i1; ++i)
-#pragma unroll
-            for (int j = 0; j < NI; ++j) {
-                if constexpr (ST) acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(b[j], a[i], acc[i][j], 0, 0, 0);
-                else acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[i], b[j], acc[i][j], 0, 0, 0);
-            }
-    };
-    // One k-tile.  On entry set 0 holds step 0 of this tile (read after the previous barrier).
-    // The next tile lands in stage (An, Bn), last read before the previous barrier, while
-    // this one is multiplied; the reads of a step precede most MFMAs of the step before it,
-    // also across the barrier: the last step's MFMAs cover the first reads of the next
-    // tile, which all wavefronts issue at once when the barrier opens.
-    auto tile_step = [&](const uint16_t* Ac, const uint16_t* Bc, uint16_t* An, uint16_t* Bn, int kt) {
-        const bool more = kt + 1 < KT;
-        if (more) fetch(An, Bn, (kt + 1) * BK);
-        __builtin_amdgcn_sched_barrier(0);
-        mfmas(af[0], bfr[0], 0, 1);
-        __builtin_amdgcn_sched_barrier(0);
-        read_frags(Ac, Bc, 1, af[1], bfr[1]);
-        __builtin_amdgcn_sched_barrier(0);
-        mfmas(af[0], bfr[0], 1, MI);
-        mfmas(af[1], bfr[1], 0, 1);
-        __builtin_amdgcn_sched_barrier(0);
-        read_frags(Ac, Bc, 2, af[0], bfr[0]);
-        __builtin_amdgcn_sched_barrier(0);
-        mfmas(af[1], bfr[1], 1, MI);
-        mfmas(af[0], bfr[0], 0, 1);
-        __builtin_amdgcn_sched_barrier(0);
-        read_frags(Ac, Bc, 3, af[1], bfr[1]);
-        __builtin_amdgcn_sched_barrier(0);
-        mfmas(af[0], bfr[0], 1, MI);
-        __builtin_amdgcn_sched_barrier(0);
-        __builtin_amdgcn_s_waitcnt(0x0f70);  // vmcnt(0): the next tile's chunks of this wavefront have landed
-        __syncthreads();                      // ... and everybody's; everybody is done reading this tile
-        __builtin_amdgcn_sched_barrier(0);
-        mfmas(af[1], bfr[1], 0, 1);
-        __builtin_amdgcn_sched_barrier(0);
-        if (more) read_frags(An, Bn, 0, af[0], bfr[0]);
-        __builtin_amdgcn_sched_barrier(0);
-        mfmas(af[1], bfr[1], 1, MI);
-        __builtin_amdgcn_sched_barrier(0);
-    };
-
-    if (kt0 < KT) fetch(A0, B0, kt0 * BK);
-    __builtin_amdgcn_s_waitcnt(0x0f70);
-    __syncthreads();
-    if (kt0 < KT) read_frags(A0, B0, 0, af[0], bfr[0]);
-    for (int kt = kt0; kt < KT; kt += 2) {
-        tile_step(A0, B0, A1, B1, kt);
-        if (kt + 1 < KT) tile_step(A1, B1, A0, B0, kt + 1);
-    }
-
-    if constexpr (ST) {
-        // the four 32 KB buffers hold rows 0-63, 64-127, 128-191, 192-255 of the bf16 tile
-        if (m0 + BM <= g.M && n0 + BN <= g.N && (g.flags & LITHOS_F_OUT_F32)) {
-            static_for<MI * NI>([&](auto ij) {
-                constexpr int i = decltype(ij)::value / NI, j = decltype(ij)::value % NI;
-                store_block_swapped_f32(g, reinterpret_cast<float*>(g.C), m0 + wm * WM + i * 32 + (lane & 31),
-                                        n0 + wn * WN + j * 32, acc[i][j], lane);
-            });
-        } else if (m0 + BM <= g.M && n0 + BN <= g.N && !(g.flags & LITHOS_F_OUT_SPLIT)) {
-            __syncthreads();
-            static_for<MI * NI>([&](auto ij) {
-                constexpr int i = decltype(ij)::value / NI, j = decltype(ij)::value % NI;
-                uint16_t* const st = wm == 0 ? (i < 2 ? A0 : A1) : (i < 2 ? B0 : B1);
-                stage_block<BN>(g, st, (i & 1) * 32 + (lane & 31), m0 + wm * WM + i * 32 + (lane & 31), wn * WN + j * 32,
-                                n0 + wn * WN + j * 32, acc[i][j], lane);
-            });
-            __syncthreads();
-            uint16_t* const C = reinterpret_cast<uint16_t*>(g.C);
-            const uint16_t* const src = wave < 2 ? A0 : wave < 4 ? A1 : wave < 6 ? B0 : B1;
-#pragma unroll 4
-            for (int it = 0; it < 16; ++it) {            // wavefront w stores rows 32w .. 32w+31, two per step
-                const int r = (wave & 1) * 32 + it * 2 + (lane >> 5), p = lane & 31;
-                const uint4 v = *reinterpret_cast<const uint4*>(src + stage_index<BN>(r, p));
-                *reinterpret_cast<uint4*>(C + (int64_t)(m0 + (wave >> 1) * 64 + r) * g.ldc + n0 + p * 8) = v;
-            }
-        } else {
-            static_for<MI * NI>([&](auto ij) {
-                constexpr int i = decltype(ij)::value / NI, j = decltype(ij)::value % NI;
-                store_block_swapped(g, m0 + wm * WM + i * 32 + (lane & 31), n0 + wn * WN + j * 32, acc[i][j], lane);
-            });
-        }
+            for (int e = 0; e < 4; ++e) epilogue_store(g, mw + i * 16 + l16, nw + j * 16 + quad * 4 + e, v[e]);
+        });
         return;
     }
-
-    static_for<MI * NI>([&](auto ij) {
-        constexpr int i = decltype(ij)::value / NI, j = decltype(ij)::value % NI;
-        const int n = n0 + wn * WN + j * 32 + (lane & 31);
-        const int mb = m0 + wm * WM + i * 32 + 4 * (lane >> 5);
-        static_for<16>([&](auto ee) {
-            constexpr int e = decltype(ee)::value;
-            epilogue_store(g, mb + 8 * (e >> 2) + (e & 3), n, acc[i][j][e]);
-        });
+    // Whole 16-byte pieces of C; what lies beyond the matrix computes on its last row and columns and is not stored.
+    const bool with_bias = g.flags & LITHOS_F_BIAS, with_gelu = g.flags & LITHOS_F_GELU, with_resid = g.flags & LITHOS_F_RESIDUAL;
+    uint16_t* const scratch = wave == 0 ? A0 : wave == 1 ? A1 : wave == 2 ? A2 : A3;     // 16 rows of 128 values of this wavefront's own
+    const auto scratch_at = [&](int r, int p) __attribute__((always_inline)) { return scratch + r * 128 + ((p ^ r) << 3); };
+    static_for<MI>([&](auto ic) __attribute__((always_inline)) {
+        constexpr int i = decltype(ic)::value;      // a strip of 16 rows
+        const int m = mw + i * 16 + l16;
+        f32x4a v[NI];
+        static_for<NI>([&](auto j) __attribute__((always_inline)) { v[j] = agpr_read(acc[i][j]); });
+        if (with_bias | with_gelu | with_resid) {
+            const float* const rrow = g.resid + (int64_t)min(m, g.M - 1) * g.ldr;
+            f32x4_u bv[NI], rv[NI];
+            if (with_bias) static_for<NI>([&](auto j) __attribute__((always_inline)) { bv[j] = *reinterpret_cast<const f32x4_u*>(g.bias + min(nw + j * 16 + quad * 4, g.N - 4)); });
+            if (with_resid) static_for<NI>([&](auto j) __attribute__((always_inline)) { rv[j] = *reinterpret_cast<const f32x4_u*>(rrow + min(nw + j * 16 + quad * 4, g.N - 4)); });
+            static_for<NI * 4>([&](auto je) __attribute__((always_inline)) {
+                constexpr int j = decltype(je)::value / 4, e = decltype(je)::value % 4;
+                if (with_bias) v[j][e] += bv[j][e];
+            });
+            if (with_gelu) static_for<NI * 4>([&](auto je) __attribute__((always_inline)) {
+                constexpr int j = decltype(je)::value / 4, e = decltype(je)::value % 4;
+                v[j][e] = gelu_erf(v[j][e]);
+            });
+            static_for<NI * 4>([&](auto je) __attribute__((always_inline)) {
+                constexpr int j = decltype(je)::value / 4, e = decltype(je)::value % 4;
+                if (with_resid) v[j][e] += rv[j][e];
+            });
+        }
+        if (g.flags & LITHOS_F_OUT_F32) {
+            float* const C = reinterpret_cast<float*>(g.C) + (int64_t)m * g.ldc;
+            static_for<NI>([&](auto j) __attribute__((always_inline)) {
+                const int n = nw + j * 16 + quad * 4;
+                if (m < g.M && n < g.N) *reinterpret_cast<f32x4a*>(C + n) = v[j];
+            });
+            return;
+        }
+        // The strip turns in LDS, so that rows of 256 bytes leave with 16 bytes per lane: row r keeps its 16-byte
+        // piece p at p ^ r.  Second plane of a split output: what the first rounding dropped.
+        const auto store = [&](auto lo, uint16_t* C) __attribute__((always_inline)) {
+            static_for<NI>([&](auto j) __attribute__((always_inline)) {
+                float x[4];
+#pragma unroll
+                for (int e = 0; e < 4; ++e) { x[e] = v[j][e]; if constexpr (decltype(lo)::value) x[e] -= bf16_to_f32(f32_to_bf16(x[e])); }
+                *reinterpret_cast<uint2*>(scratch_at(l16, j * 2 + (quad >> 1)) + 4 * (quad & 1)) = make_uint2(pack_bf16(x[0], x[1]), pack_bf16(x[2], x[3]));
+            });
+            wave_lds_sync();
+#pragma unroll
+            for (int t = 0; t < 4; ++t) {
+                const int r = t * 4 + quad, mr = mw + i * 16 + r, n = nw + l16 * 8;
+                const uint4 w = *reinterpret_cast<const uint4*>(scratch_at(r, l16));
+                if (mr < g.M && n < g.N) *reinterpret_cast<uint4*>(C + (int64_t)mr * g.ldc + n) = w;
+            }
+            wave_lds_sync();
+        };
+        store(std::false_type{}, reinterpret_cast<uint16_t*>(g.C));
+        if (g.flags & LITHOS_F_OUT_SPLIT) store(std::true_type{}, reinterpret_cast<uint16_t*>(g.C) + g.c_plane);
     });
+#endif
 }
-
-#define LITHOS_LDS256_PICK(ST)                                                                                              \
-    (ta ? (tb ? (gemm_fn)gemm_lds256_kernel<2, 4, ST, true, false> : (gemm_fn)gemm_lds256_kernel<2, 4, ST, true, true>)    \
-        : (tb ? (gemm_fn)gemm_lds256_kernel<2, 4, ST, false, false> : (gemm_fn)gemm_lds256_kernel<2, 4, ST, false, true>))
 
 } // namespace lithos

@@ -186,15 +186,6 @@ void gemm_skinny_kernel(GemmArgs g, AtomArgs atom)
 // On a 64-CU partition a large weight matrix streams at that partition's read ceiling and
 // the vector ALUs are the next limit, so the loop is kept lean: nothing is masked but the
 // activations, and no load sits under a condition.
-__device__ __forceinline__ void wave_lds_sync()
-{
-    // LDS operations of one wavefront complete in order; this only stops the compiler
-    // from moving reads of other lanes' data across the writes
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
-
 // NORM: 0 = activations as stored; NORM_RMS / NORM_LN = the GEMM of the normalised rows, without a
 // pass over the rows before the first chunk.  A row's statistics scale and shift whole output rows,
 // so they can wait for the epilogue:
