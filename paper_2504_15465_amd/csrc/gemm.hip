@@ -5,8 +5,11 @@
 //  * gemm_lds256_kernel (gemm_lds256.hpp, gemm_lds256{,_ta}.hip) - 256x256 tiles, K % 64 == 0, any operand
 //    layout: global memory straight into LDS, k-strided operands read with the
 //    transposing LDS load; the best-effort and training-shaped GEMMs;
-//  * gemm_lds_kernel (gemm_lds.hpp, gemm_tile{64,128}.hip) - 64 and 128 tiles, any K % 8 == 0, split-bf16 A;
-//    global memory straight into LDS, two or three stages;
+//  * gemm_lds256w8_kernel (gemm_lds256w8.hpp) - the same tiles by eight wavefronts, for an epilogue and element-wise stores;
+//  * gemm_mid_kernel (gemm_mid.hpp, gemm_tile128.hip, gemm_mid192.hip) - 128x128 and 64x192 tiles, any K % 8 == 0,
+//    split-bf16 A; global memory straight into LDS, three or four stages;
+//  * gemm_lds_kernel (gemm_lds.hpp, gemm_tile{64,128}.hip) - 64 tiles, any K % 8 == 0, split-bf16 A, and 128 tiles of two
+//    k-contiguous operands with a long K; global memory straight into LDS, two or three stages;
 //  * gemm_tile_kernel (gemm_tile.hpp, gemm_tile256_{wide,elem}.hip) - 256 tiles with any other K, through registers;
 //  * gemm_skinny_*_kernel (gemm_skinny.hip) - M <= 32 rows (bf16 or fp32
 //    activations) against a [N,K] bf16 weight matrix: HBM-bound, the weights are
@@ -26,9 +29,26 @@ namespace lithos {
 
 // ---- host side -------------------------------------------------------------
 
-constexpr int64_t LDS256_MAX_LD = 1 << 22;      // elements: 256 rows are 2 GiB
+// The 128, 64x192 and 256 tiles address their operands with 32-bit byte offsets from the tile's first row: 256 rows of this
+// many elements are 2 GiB.  Longer rows take the kernels with 64-bit addresses.
+constexpr int64_t MAX_OFFSET_LD = 1 << 22;
 
-static int tile_threads(int variant) { return variant == V_TILE64 || variant == V_TILE128 || variant == V_LDS256 ? 256 : 512; }
+// A tile shape that auto_tile alone chooses.
+constexpr int TILE_64X192 = 64192;
+
+// The tile of a GEMM that names none.
+static int auto_tile(int64_t M, int64_t N, bool split)
+{
+    const auto blocks = [&](int64_t bm, int64_t bn) { return ((M + bm - 1) / bm) * ((N + bn - 1) / bn); };
+    // Split A (us, 64x192 / 128x128 / 64x64): 4096 x 2304 x 768 31.1 / 36.7 / 48, 4096 x 768 x 3072 35.9 / 43.2 / 57,
+    // 4096 x 3072 x 768 39.3 / 38.4 / 62, 1024 x 2304 x 768 (192 blocks) 10.5 / 12.1 / 16.3; 64 blocks or fewer leave too
+    // much of the chip idle: 1024 x 768 x 3072 31.6 / 40.2 / 21.3.
+    if (split) return blocks(64, 192) >= 128 ? TILE_64X192 : 64;
+    if (blocks(128, 128) < 128) return 64;
+    return blocks(256, 256) >= 256 ? 256 : 128;
+}
+
+static int tile_threads(int variant) { return variant == V_TILE64 || variant == V_TILE128 || variant == V_MID192 || variant == V_TILE128_DEEP || variant == V_LDS256 ? 256 : 512; }
 
 // full bf16 tiles can leave through LDS when whole 16-byte pieces of C rows are addressable
 // (fp32 tiles of the same kernels are stored from registers, 16 bytes per lane)
@@ -45,9 +65,12 @@ static gemm_fn variant_fn(int variant, bool ta, bool tb, bool a32, bool split, b
 {
     switch (variant) {
     case V_LDS256: return ta ? gemm_lds256_ta_fn(tb) : gemm_lds256_fn(tb);
+    case V_LDS256W8: return st ? gemm_lds256w8_wide_fn(ta, tb) : gemm_lds256w8_elem_fn(ta, tb);
     case V_TILE64: return gemm_tile64_fn(ta, tb, split, st, false);
     case V_TILE64_2K: return gemm_tile64_fn(ta, tb, split, st, true);
-    case V_TILE128: return gemm_tile128_fn(ta, tb, split, st);
+    case V_TILE128: return gemm_tile128_fn(ta, tb, split);
+    case V_TILE128_DEEP: return gemm_tile128_deep_fn(st);
+    case V_MID192: return gemm_mid192_fn(tb);
     case V_TILE256: return st ? gemm_tile256_wide_fn(ta, tb) : gemm_tile256_elem_fn(ta, tb);
     default: return gemm_skinny_fn(variant, a32, norm);
     }
@@ -93,9 +116,7 @@ int gemm_plan(const lithos_op_t& op, OpPlan* plan)
         return fail(LITHOS_EINVAL, "gemm: fp32 activations (IN_F32) are only taken by the skinny kernel (M <= 32, TRANS_B)");
     if (tile == 0) {
         if (M <= 32 && tb && !ta && slices <= 1) tile = LITHOS_TILE_SKINNY;
-        else if (!split && ((M + 255) / 256) * ((N + 255) / 256) >= 256) tile = 256;
-        else if (((M + 127) / 128) * ((N + 127) / 128) >= 128) tile = 128;
-        else tile = 64;
+        else tile = auto_tile(M, N, split);
     }
     int variant;
     if (tile == LITHOS_TILE_SKINNY) {
@@ -119,13 +140,25 @@ int gemm_plan(const lithos_op_t& op, OpPlan* plan)
             if (2 * N * ldb * 2 >= (1ll << 32)) return fail(LITHOS_EINVAL, "gemm: the skinny kernel addresses weight rows with 32-bit byte offsets (2N*ldb*2 < 4 GiB with GLU)");
         }
         plan->grid = {(uint32_t)(glu ? (N + 15) / 16 : (N + 16 * SKINNY_NB - 1) / (16 * SKINNY_NB)), 1, 1};
-    } else if (tile == 64 || tile == 128 || tile == 256) {
+    } else if (tile == 64 || tile == 128 || tile == 256 || tile == TILE_64X192) {
         if (fused) return fail(LITHOS_EINVAL, "gemm: NORM_LN, NORM_RMS and GLU are built into the weight-streaming kernel only (TRANS_B, M <= 16)");
         if (split && tile == 256) return fail(LITHOS_EINVAL, "gemm: SPLIT_A is built for the 64 and 128 tiles only");
-        variant = tile == 64 ? V_TILE64 : tile == 128 ? V_TILE128 : V_TILE256;
-        // the kernel's 32-bit byte offsets reach 256 rows of this length
-        if (tile == 256 && K % 64 == 0 && lda <= LDS256_MAX_LD && ldb <= LDS256_MAX_LD) variant = V_LDS256;
-        plan->grid = {(uint32_t)((N + tile - 1) / tile), (uint32_t)((M + tile - 1) / tile), (uint32_t)(slices > 1 ? slices : 1)};
+        const bool long_rows = lda > MAX_OFFSET_LD || ldb > MAX_OFFSET_LD;
+        if (long_rows && tile != 256) tile = 64;
+        variant = tile == 64 ? V_TILE64 : tile == 128 ? V_TILE128 : tile == 256 ? V_TILE256 : V_MID192;
+        // Stores of single elements (a row or its last tile that does not divide into 16-byte pieces) are slower from the
+        // layouts of the 16x16x32 kernels.
+        const bool pieces = staged_epilogue(op) && N % 8 == 0;
+        // Four wavefronts gain 15 % in the loop and lose in an epilogue, 5 us a tile with bias and residual and 13 with GELU (us, four /
+        // eight wavefronts: 2048 x 2048 x 512 with bias 24 / 18, with residual too 36 / 25, with GELU too 47 / 31; 4096 x 4096 x 1024 with
+        // bias and residual 55 / 44; with all three 4096 x 8192 x 4096 284 / 265, 256 x 256 x 8192 167 / 165).
+        if (tile == 256 && K % 64 == 0) variant = long_rows || !pieces || (op.flags & (LITHOS_F_BIAS | LITHOS_F_GELU | LITHOS_F_RESIDUAL)) ? V_LDS256W8 : V_LDS256;
+        // Both operands k-contiguous and K long: with several workgroups on a CU the half lines of 32-deep k-tiles cost more than
+        // the rest of the kernel gains (us, 32 / 64 deep, on 64 CUs: 512 x 4096 x 4096 57 / 50, 200 x 6000 x 6000 113 / 90,
+        // 2048^3 52 / 54; on 256 CUs 33 / 46, 62 / 75, 22 / 28).
+        if (variant == V_TILE128 && !split && !ta && tb && (K > 2048 || !pieces)) variant = V_TILE128_DEEP;
+        const int64_t bm = tile == TILE_64X192 ? 64 : tile, bn = tile == TILE_64X192 ? 192 : tile;
+        plan->grid = {(uint32_t)((N + bn - 1) / bn), (uint32_t)((M + bm - 1) / bm), (uint32_t)(slices > 1 ? slices : 1)};
         // The 64 tile splits K between two groups of wavefronts while all blocks of the whole grid (never of an atom: the
         // sums must not depend on the cut) find room at two per CU of the whole chip: then the chain of k-tiles is the
         // time (us, two groups / one: 1024 x 1024 x 8192 NN 47 / 65, split 128 x 768 x 3072 19 / 22).  More blocks hide it,

@@ -1,9 +1,9 @@
 #pragma once
-#include "gemm_common.hpp"
+#include "gemm_mfma16.hpp"
 
 namespace lithos {
 
-// ---- 256x256 tile, K a multiple of 64, any operand layout ---------------------------
+// ---- 256x256 tile, K a multiple of 64, any operand layout, plain stores of 16-byte pieces ----------
 // Four wavefronts of 128x128, one per SIMD: 256 accumulator registers and 256 for the rest.
 //
 // What bounds it: on random data the chip lowers its clock with the power that the MFMAs and everything around them
@@ -31,22 +31,13 @@ namespace lithos {
 // the MFMA operand layout.  Two such loads make a fragment; nothing is transposed in registers.
 //
 // 8192^3 NN 864 -> 735 us (1495 TFLOP/s; eight wavefronts of 128x64, 64-deep tiles, before), 4096^3 111 -> 96,
-// 16384 x 1024 x 4096 NT 121 -> 105, 16384 x 4096 x 1024 NN 131 -> 122.
-
-typedef float f32x4a __attribute__((ext_vector_type(4)));
+// 16384 x 1024 x 4096 NT 121 -> 104, 16384 x 4096 x 1024 NN 131 -> 116.
 
 // The compiler does not see the latency of an MFMA written here: the accumulators are first read by other
 // instructions behind the loop's last barrier and mfma16_settle.
 __device__ __forceinline__ void mfma16_agpr(f32x4a& c, bf16x8 x, bf16x8 y)
 {
     asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+a"(c) : "v"(x), "v"(y));
-}
-// A block of accumulators in vector registers, from here on: copies of all 64 blocks ahead of the epilogue's first branch
-// would go to memory.
-__device__ __forceinline__ f32x4a agpr_read(f32x4a& c)
-{
-    asm volatile("" : "+a"(c));
-    return c;
 }
 __device__ __forceinline__ void mfma16_settle() { asm volatile("s_nop 15\n\ts_nop 15" ::: "memory"); }
 
@@ -206,73 +197,7 @@ void gemm_lds256_kernel(GemmArgs g, AtomArgs atom)
     turn(std::integral_constant<int, 0>{});         // the stages are free
     mfma16_settle();
 
-    // lane: row l16 of a 16x16 block, columns 4 quad .. +3
-    const int mw = m0 + wm * 128, nw = n0 + wn * 128;
-    if (!g.wide || ((g.N & 7) && n0 + BN > g.N)) {  // element by element
-        static_for<MI * NI>([&](auto ij) __attribute__((always_inline)) {
-            constexpr int i = decltype(ij)::value / NI, j = decltype(ij)::value % NI;
-            const f32x4a v = agpr_read(acc[i][j]);
-#pragma unroll
-            for (int e = 0; e < 4; ++e) epilogue_store(g, mw + i * 16 + l16, nw + j * 16 + quad * 4 + e, v[e]);
-        });
-        return;
-    }
-    // Whole 16-byte pieces of C; what lies beyond the matrix computes on its last row and columns and is not stored.
-    const bool with_bias = g.flags & LITHOS_F_BIAS, with_gelu = g.flags & LITHOS_F_GELU, with_resid = g.flags & LITHOS_F_RESIDUAL;
-    uint16_t* const scratch = wave == 0 ? A0 : wave == 1 ? A1 : wave == 2 ? A2 : A3;     // 16 rows of 128 values of this wavefront's own
-    const auto scratch_at = [&](int r, int p) __attribute__((always_inline)) { return scratch + r * 128 + ((p ^ r) << 3); };
-    static_for<MI>([&](auto ic) __attribute__((always_inline)) {
-        constexpr int i = decltype(ic)::value;      // a strip of 16 rows
-        const int m = mw + i * 16 + l16;
-        f32x4a v[NI];
-        static_for<NI>([&](auto j) __attribute__((always_inline)) { v[j] = agpr_read(acc[i][j]); });
-        if (with_bias | with_gelu | with_resid) {
-            const float* const rrow = g.resid + (int64_t)min(m, g.M - 1) * g.ldr;
-            f32x4_u bv[NI], rv[NI];
-            if (with_bias) static_for<NI>([&](auto j) __attribute__((always_inline)) { bv[j] = *reinterpret_cast<const f32x4_u*>(g.bias + min(nw + j * 16 + quad * 4, g.N - 4)); });
-            if (with_resid) static_for<NI>([&](auto j) __attribute__((always_inline)) { rv[j] = *reinterpret_cast<const f32x4_u*>(rrow + min(nw + j * 16 + quad * 4, g.N - 4)); });
-            static_for<NI * 4>([&](auto je) __attribute__((always_inline)) {
-                constexpr int j = decltype(je)::value / 4, e = decltype(je)::value % 4;
-                if (with_bias) v[j][e] += bv[j][e];
-            });
-            if (with_gelu) static_for<NI * 4>([&](auto je) __attribute__((always_inline)) {
-                constexpr int j = decltype(je)::value / 4, e = decltype(je)::value % 4;
-                v[j][e] = gelu_erf(v[j][e]);
-            });
-            static_for<NI * 4>([&](auto je) __attribute__((always_inline)) {
-                constexpr int j = decltype(je)::value / 4, e = decltype(je)::value % 4;
-                if (with_resid) v[j][e] += rv[j][e];
-            });
-        }
-        if (g.flags & LITHOS_F_OUT_F32) {
-            float* const C = reinterpret_cast<float*>(g.C) + (int64_t)m * g.ldc;
-            static_for<NI>([&](auto j) __attribute__((always_inline)) {
-                const int n = nw + j * 16 + quad * 4;
-                if (m < g.M && n < g.N) *reinterpret_cast<f32x4a*>(C + n) = v[j];
-            });
-            return;
-        }
-        // The strip turns in LDS, so that rows of 256 bytes leave with 16 bytes per lane: row r keeps its 16-byte
-        // piece p at p ^ r.  Second plane of a split output: what the first rounding dropped.
-        const auto store = [&](auto lo, uint16_t* C) __attribute__((always_inline)) {
-            static_for<NI>([&](auto j) __attribute__((always_inline)) {
-                float x[4];
-#pragma unroll
-                for (int e = 0; e < 4; ++e) { x[e] = v[j][e]; if constexpr (decltype(lo)::value) x[e] -= bf16_to_f32(f32_to_bf16(x[e])); }
-                *reinterpret_cast<uint2*>(scratch_at(l16, j * 2 + (quad >> 1)) + 4 * (quad & 1)) = make_uint2(pack_bf16(x[0], x[1]), pack_bf16(x[2], x[3]));
-            });
-            wave_lds_sync();
-#pragma unroll
-            for (int t = 0; t < 4; ++t) {
-                const int r = t * 4 + quad, mr = mw + i * 16 + r, n = nw + l16 * 8;
-                const uint4 w = *reinterpret_cast<const uint4*>(scratch_at(r, l16));
-                if (mr < g.M && n < g.N) *reinterpret_cast<uint4*>(C + (int64_t)mr * g.ldc + n) = w;
-            }
-            wave_lds_sync();
-        };
-        store(std::false_type{}, reinterpret_cast<uint16_t*>(g.C));
-        if (g.flags & LITHOS_F_OUT_SPLIT) store(std::true_type{}, reinterpret_cast<uint16_t*>(g.C) + g.c_plane);
-    });
+    epilogue_plain16<true>(g, acc, m0 + wm * 128, n0 + wn * 128, lane, wave == 0 ? A0 : wave == 1 ? A1 : wave == 2 ? A2 : A3);
 #endif
 }
 
