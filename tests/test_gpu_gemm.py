@@ -811,3 +811,57 @@ def test_padding_between_rows_is_never_used(tile, split, ta, tb, k):
             assert np.abs(got.double().cpu().numpy() - ref).max() <= bound
         else:
             bf16_close(got, ref, abs_tol=bound)
+
+
+@pytest.mark.parametrize("m,n,k,tb,grid", [
+    (33, 200, 72, False, (4, 2, 1)),        # 32x64 tiles: a second row of tiles with one row; one chunk of K and an eighth
+    (100, 1000, 520, True, (16, 4, 1)),     # 64 of them; k-contiguous B; nine chunks, the last of 8
+    (64, 64, 8, False, (1, 2, 1)),          # fewer chunks than wavefronts
+    (65, 500, 264, True, (8, 3, 1)),        # rows of C in 8-byte pieces only: element by element
+    (128, 768, 3072, False, (12, 4, 1)),    # the encoder's longest sum
+    (520, 3080, 136, False, (17, 9, 1)),    # 64x192 tiles, ragged in every direction
+    (1100, 1500, 40, True, (8, 18, 1)),     # k-contiguous B, element by element, K shorter than the stages
+    (2048, 768, 224, False, (4, 32, 1)),    # 64x192: whole tiles, seven k-tiles of 32
+])
+def test_split_activations_in_tiles_chosen_by_size(m, n, k, tb, grid):
+    """A split A without a named tile: every output form, with and without epilogue, inside a larger buffer of NaN."""
+    x32 = inputs.normal_f32((m, k), 70)
+    hi = inputs.to_bf16_bits(x32)
+    lo = inputs.to_bf16_bits(x32 - O.bf16_to_f64(hi).astype(np.float32))
+    b_bits = inputs.normal_bits((n, k) if tb else (k, n), 71, 0.05)
+    a_val = O.bf16_to_f64(hi) + O.bf16_to_f64(lo)
+    bias, resid = inputs.normal_f32((n,), 72), inputs.normal_f32((m, n), 73)
+    plain = O.gemm(a_val, b_bits, tb=tb)
+    full = O.bias_act(plain, bias, gelu=True) + resid
+    a, b = dev_bits(np.stack([hi, lo])), dev_bits(b_bits)
+    epi = dict(bias=torch.from_numpy(bias).cuda(), gelu=True, residual=torch.from_numpy(resid).cuda())
+    ldc = n + 8
+    for ref, kw in ((plain, {}), (full, epi)):
+        c32 = nan_like((m + 1, ldc), torch.float32)
+        pair = nan_like((2, m, ldc), torch.bfloat16)
+        op = B.gemm_op(a, b, c32, m, n, k, tb=tb, a_split=True, ldc=ldc, **kw)
+        assert B.lithos_op_grid(ctx(), op)[0] == grid
+        torch.cuda.synchronize()
+        B.lithos_launch_atomized(ctx(), op, (0, 0, 0), 5)
+        B.lithos_launch_atomized(ctx(), B.gemm_op(a, b, pair, m, n, k, tb=tb, a_split=True, c_split=True, ldc=ldc, **kw))
+        B.lithos_partition_sync(ctx(), None)
+        # fp32 sums of k products: 2^-24 of the sum of magnitudes per addition, which a random walk of sqrt(k) steps passes on
+        assert rel_fro(c32[:m, :n], ref) <= 1e-6
+        got = pair[0, :m, :n].cpu().to(torch.float64).numpy() + pair[1, :m, :n].cpu().to(torch.float64).numpy()
+        assert np.abs(got - ref).max() <= 2.0 ** -15 * np.abs(ref).max() + 1e-6
+        assert torch.isnan(c32[m:]).all() and torch.isnan(c32[:, n:]).all() and torch.isnan(pair[:, :, n:]).all()
+
+
+@pytest.mark.parametrize("tile,split", [(64, False), (128, False), (256, False), (0, True), (64, True), (128, True)])
+def test_rows_longer_than_32_bit_offsets(tile, split):
+    """Rows of more than 4M elements take the kernels with 64-bit addresses, whatever tile is named."""
+    m, n, k, ld = 3, 72, 64, (1 << 22) + 8
+    a_bits, b_bits = inputs.normal_bits((m, k), 80), inputs.normal_bits((k, n), 81)
+    a = torch.zeros((2 if split else 1, m, ld), dtype=torch.bfloat16, device="cuda")
+    a[0, :, :k] = dev_bits(a_bits)
+    c = nan_like((m, n), torch.float32)
+    torch.cuda.synchronize()
+    op = B.gemm_op(a, dev_bits(b_bits), c, m, n, k, lda=ld, tile=tile, a_split=split)
+    B.lithos_launch_atomized(ctx(), op)
+    B.lithos_partition_sync(ctx(), None)
+    assert rel_fro(c, O.gemm(a_bits, b_bits)) <= 1e-6
