@@ -3,8 +3,9 @@
 // Such a grid leaves each CU one tile and nothing to hide its latencies with; every launch finds the L2 of a die cold, so the chain
 // of k-tiles waits for what lies behind it, about 0.8 us each time.  So the four wavefronts split K between them, chunk c of 64
 // going to wavefront c % 4, and each fetches two chunks at a time into its own LDS (128 KB in flight per CU),
-// without a barrier until their sums are added, in wavefront order.  128 x 768 x 3072 with bias and residual 11.5 us against
-// 16.8 with 64x64 tiles (24 tiles, two groups of wavefronts), 128 x 1024 x 1024 7.0 against 8.5, 128 x 768 x 768 7.0 against 7.4.
+// without a barrier until their sums are added, in wavefront order.  128 x 768 x 3072 with bias and residual 12.2 us against
+// 16.8 with 64x64 tiles (24 tiles, two groups of wavefronts), 128 x 1024 x 1024 7.1 against 8.5, 128 x 768 x 768 6.3 against 7.4.
+// The same for plain operands in 64x64 tiles is slower up to K = 4096 (512^3 6.6 / 5.3, 512 x 512 x 4096 17.0 / 16.0).
 #include "gemm_mfma16.hpp"
 
 namespace lithos {
@@ -104,31 +105,37 @@ void gemm_thin_kernel(GemmArgs g, AtomArgs atom)
             }
         }
     };
-    fetch(A0, B0);
-    fetch(A1, B1);
-    for (int k = wave * BK; k < g.K; k += 8 * BK) {  // two chunks a turn; one behind the end is all zeros
-        __builtin_amdgcn_sched_barrier(0);
-        __builtin_amdgcn_s_waitcnt(0x0f70);          // vmcnt(0): both chunks have landed
-        asm volatile("" ::: "memory");
-        read(0, A0, B0);
-        read(1, A1, B1);
-        __builtin_amdgcn_sched_barrier(0);
-        __builtin_amdgcn_s_waitcnt(0xc07f);          // lgkmcnt(0): both have been read and can be filled again
-        asm volatile("" ::: "memory");
-        __builtin_amdgcn_sched_barrier(0);
-        fetch(A0, B0);
-        fetch(A1, B1);
+    const auto multiply = [&](int x) __attribute__((always_inline)) {
 #pragma unroll
-        for (int x = 0; x < 4; ++x)
+        for (int kk = 0; kk < 2; ++kk)
 #pragma unroll
             for (int p = 1; p >= 0; --p)             // the small plane first
 #pragma unroll
                 for (int i = 0; i < MI; ++i)
 #pragma unroll
                     for (int j = 0; j < NI; ++j)     // operands exchanged: a lane holds four consecutive columns of one row of C
-                        acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(bf[x >> 1][x & 1][j], af[x >> 1][x & 1][p][i], acc[i][j], 0, 0, 0);
+                        acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(bf[x][kk][j], af[x][kk][p][i], acc[i][j], 0, 0, 0);
+    };
+    // Chunks that do not exist are neither fetched nor multiplied: loads without a lane inside their buffer take time too
+    // (128 x 768 x 768 7.0 us with them, 6.3 without).
+    int chunks = ((g.K + BK - 1) / BK - wave + 3) / 4;       // this wavefront's
+    if (chunks > 0) fetch(A0, B0);
+    if (chunks > 1) fetch(A1, B1);
+    for (; chunks > 0; chunks -= 2) {                // two a turn
+        __builtin_amdgcn_sched_barrier(0);
+        __builtin_amdgcn_s_waitcnt(0x0f70);          // vmcnt(0): both have landed
+        asm volatile("" ::: "memory");
+        read(0, A0, B0);
+        if (chunks > 1) read(1, A1, B1);
+        __builtin_amdgcn_sched_barrier(0);
+        __builtin_amdgcn_s_waitcnt(0xc07f);          // lgkmcnt(0): both have been read and can be filled again
+        asm volatile("" ::: "memory");
+        __builtin_amdgcn_sched_barrier(0);
+        if (chunks > 2) fetch(A0, B0);
+        if (chunks > 3) fetch(A1, B1);
+        multiply(0);
+        if (chunks > 1) multiply(1);
     }
-    __builtin_amdgcn_s_waitcnt(0x0070);              // the zero chunks behind the last have landed too
     __syncthreads();
 
     // the wavefronts' sums, [32][64] each, 16-byte chunk c of row r at c ^ (r % 8)
