@@ -47,8 +47,8 @@ HBM_PEAK_GBS = 8000.0
 # HBM bytes per whole 8192^3 launch, by GEMM tile: rocprofv3 --pmc FETCH_SIZE and WRITE_SIZE (KiB per dispatch),
 # each scaled by what the same counter reads for a 1 GiB device-to-device copy (fetch x 2.00, write x 1.00).
 # Source: profiles/gemm_lds256_8192_and_cfg2_stacking.md, section 3 (256 tiles: 786859 KiB x 2 + 131072 KiB), and
-# profiles/tile_gemms_and_encoder.md (128 tiles: 1475103 KiB x 2 + 131072 KiB).
-TRAFFIC_BYTES = {256: 1.75e9, 128: 3.16e9}
+# profiles/tile_gemms_and_encoder.md (128 tiles: 1731207 KiB x 2 + 131072 KiB).
+TRAFFIC_BYTES = {256: 1.75e9, 128: 3.68e9}
 ALGORITHMIC_BYTES_8192 = 3 * 8192 * 8192 * 2.0      # A and B read once, C written once, bf16
 TAIL_REQUESTS, TAIL_WARMUP = 2000, 100              # fixed-size legs behind "tail_study" (p99 needs samples)
 TAIL_REQUESTS_LONG, TAIL_WARMUP_LONG = 5000, 200    # the two legs whose tails are compared: static masks, full scheduler
@@ -97,7 +97,7 @@ def be_gemm_8192(B, inputs, torch, tile):
     a, b = inputs.bits_to_torch(a_bits, "cuda").contiguous(), inputs.bits_to_torch(b_bits, "cuda").contiguous()
     c = torch.empty((n, n), dtype=torch.bfloat16, device="cuda")
     op = B.gemm_op(a, b, c, n, n, n, tile=tile)
-    desc = ("gemm_lds256_kernel" if tile == 256 else "gemm_lds_kernel<%d,%d>" % (tile, tile)) + \
+    desc = ("gemm_lds256_kernel" if tile == 256 else "gemm_mid_kernel<128,128>" if tile == 128 else "gemm_lds_kernel<%d,%d>" % (tile, tile)) + \
         " 8192^3 bf16 (A [M,K], B [K,N]), whole launch, 256 CUs"
     return dict(ops=[op], flop=2.0 * n ** 3, dominant=(op, 2.0 * n ** 3, desc), host=(a_bits, b_bits),
                 text="bf16 8192^3 GEMMs back to back")

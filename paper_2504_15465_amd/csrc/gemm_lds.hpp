@@ -1,4 +1,4 @@
-// Direct-to-LDS MFMA tile GEMM (v_mfma_f32_32x32x16_bf16), 64x64 and 128x128 output tiles, any operand
+// Direct-to-LDS MFMA tile GEMM (v_mfma_f32_32x32x16_bf16), 64x64 (and some 128x128) output tiles, any operand
 // layout, any K % 8 == 0, split-bf16 A.  Every workgroup computes the tile named by its LOGICAL block
 // index (LithOS Section 4.4).
 #pragma once
@@ -38,12 +38,11 @@ constexpr int wait_imm(int n) { return (n & 15) | 0x70 | ((n >> 4) << 14); }
 // wavefront and instruction) S - 1 tiles ahead, with one barrier per tile; operand fragments of step kk + 1 are
 // read before the MFMAs of step kk, across the barrier too.  A chunk beyond K is fetched from gemm_zero_chunk.
 //
-// Bound by latency: on the encoder's shapes the MFMA pipes are busy 36 % (768 tiles, split A), 28 % (192 tiles, K = 3072) and
-// 23 % (768 tiles, plain) of the cycles, the LDS 11 to 16 %.  Against the form that staged through registers into one
-// buffer: 1003 x 3000 x 1160 with epilogue 59 -> 26.5 us, split 4096 x 3072 x 768 62 us (620 TFLOP/s of its two
-// products), encoder of 12 layers at 4096 tokens 3645 -> 2768 us, at 128 tokens on 64 CUs 1669 -> 1164 us.  One 64-deep
-// k-tile more in flight for the 128 tile (144 KB of LDS, one workgroup per CU) is 12 % faster with 192 tiles on 256 CUs
-// and 2-20 % slower with more tiles per CU, so two workgroups per CU it is.
+// Bound by the latency of the chain of k-tiles: what a k-tile brings is new to the die's L2, about 0.65 us a tile for grids of
+// a few blocks whatever the number of stages.  Against the form that staged through registers into one buffer 512^3 in eight
+// atoms on 32 CUs 55 -> 41 us.  Larger tiles, and a split A in grids of more or fewer tiles, are gemm_mid_kernel's and
+// gemm_thin_kernel's; 128 tiles of two k-contiguous operands with a long K stay here, whose 64-deep k-tiles read whole
+// 128-byte lines.
 template <int BM, int BN, int WGM, int WGN, int KG, int BK, int S, int MINW, bool TA, bool TB, bool SPLIT, bool ST>
 __global__ __launch_bounds__(WGM * WGN * KG * 64, MINW)
 void gemm_lds_kernel(GemmArgs g, AtomArgs atom)

@@ -1,5 +1,5 @@
 // 128x128-tile instances of the mid-size MFMA GEMM: two workgroups per CU (64 KB of LDS in four stages; a split A, with two
-// planes, 72 KB in three).
+// planes, 72 KB in three).  Beside them the 64-deep form of gemm_lds_kernel.
 #include "gemm_lds.hpp"
 #include "gemm_mid.hpp"
 
