@@ -73,7 +73,7 @@ enum {
 #define LITHOS_F_NORM_RMS  (1u << 10)  /* GEMM: rows of A pass through RMSNORM (w in[4], eps fparam0) on load */
 #define LITHOS_F_GLU       (1u << 11)  /* GEMM: B holds N gate rows then N up rows; C = silu(A gate^T) * (A up^T) */
 
-/* GEMM tile selectors for lithos_op_t.tile (0 = library chooses) */
+/* GEMM tile selectors for lithos_op_t.tile (0 = library chooses, for SPLIT_A also 64x192 and 32x64 tiles) */
 #define LITHOS_TILE_64     64    /* 64x64 output tile */
 #define LITHOS_TILE_128    128   /* 128x128 */
 #define LITHOS_TILE_256    256   /* 256x256 */
