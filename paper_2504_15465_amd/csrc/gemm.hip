@@ -115,6 +115,9 @@ int gemm_plan(const lithos_op_t& op, OpPlan* plan)
     const int norm = norm_of(op.flags);
     const bool glu = op.flags & LITHOS_F_GLU, fused = norm || glu;
     int tile = op.tile;
+    // What a caller may name.  The shapes that auto_tile alone chooses are built for fewer descriptors and not checked for below.
+    if (tile != 0 && tile != LITHOS_TILE_SKINNY && tile != 64 && tile != 128 && tile != 256)
+        return fail(LITHOS_EINVAL, "gemm: unknown tile selector %d", tile);
     if (a32 && !(M <= 32 && tb && !ta && (tile == 0 || tile == LITHOS_TILE_SKINNY)))
         return fail(LITHOS_EINVAL, "gemm: fp32 activations (IN_F32) are only taken by the skinny kernel (M <= 32, TRANS_B)");
     if (tile == 0) {
@@ -143,7 +146,7 @@ int gemm_plan(const lithos_op_t& op, OpPlan* plan)
             if (2 * N * ldb * 2 >= (1ll << 32)) return fail(LITHOS_EINVAL, "gemm: the skinny kernel addresses weight rows with 32-bit byte offsets (2N*ldb*2 < 4 GiB with GLU)");
         }
         plan->grid = {(uint32_t)(glu ? (N + 15) / 16 : (N + 16 * SKINNY_NB - 1) / (16 * SKINNY_NB)), 1, 1};
-    } else if (tile == 64 || tile == 128 || tile == 256 || tile == TILE_64X192 || tile == TILE_32X64) {
+    } else {
         if (fused) return fail(LITHOS_EINVAL, "gemm: NORM_LN, NORM_RMS and GLU are built into the weight-streaming kernel only (TRANS_B, M <= 16)");
         if (split && tile == 256) return fail(LITHOS_EINVAL, "gemm: SPLIT_A is built for the 64 and 128 tiles only");
         const bool long_rows = lda > MAX_OFFSET_LD || ldb > MAX_OFFSET_LD;
@@ -172,8 +175,6 @@ int gemm_plan(const lithos_op_t& op, OpPlan* plan)
         // of 512 36 / 41); atoms are whole waves of resident workgroups.
         const uint64_t blocks = (uint64_t)plan->grid.x * plan->grid.y * plan->grid.z;
         if (tile == 64 && (blocks <= 512 || (!split && K / plan->grid.z > 4096))) variant = V_TILE64_2K;
-    } else {
-        return fail(LITHOS_EINVAL, "gemm: unknown tile selector %d", tile);
     }
     plan->total = plan->grid.x * plan->grid.y * plan->grid.z;
     plan->threads = tile_threads(variant);

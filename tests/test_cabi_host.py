@@ -1,6 +1,7 @@
 """CPU-only checks of the C-ABI library: it loads, exports every symbol the
 header declares, and its scheduler policy core takes the same decisions as the
 oracle's scheduler model on the same scenario (no compute calls, no GPU)."""
+import ctypes
 import os
 import random
 import re
@@ -26,6 +27,36 @@ def test_gemm_split_hint_fills_the_partition():
     assert hint(8, 4096, 4096, 64) == (0, 1)              # weight-streaming shapes are not cut
     with pytest.raises(B.LithosError):
         B.lithos_gemm_split_hint(B.make_op(B.OP_SPIN, (4, 10)), 64)
+
+
+class _Plan(ctypes.Structure):
+    """OpPlan of the library: what the validator of an operator chose."""
+    _fields_ = [("grid", ctypes.c_uint32 * 3), ("total", ctypes.c_uint32), ("threads", ctypes.c_uint32),
+                ("wg_per_cu", ctypes.c_uint32), ("variant", ctypes.c_int)]
+
+
+def gemm_plan(op):
+    """(return code, plan) of the host-side validator of GEMM descriptors; launches nothing."""
+    plan = _Plan()
+    rc = B.lib()["_ZN6lithos9gemm_planERK9lithos_opPNS_6OpPlanE"](ctypes.byref(op), ctypes.byref(plan))
+    return rc, plan
+
+
+def gemm(m, n, k, **kw):
+    """A descriptor with addresses that nothing reads."""
+    return B.gemm_op(4096, 8192, 16384, m, n, k, **kw)
+
+
+@pytest.mark.parametrize("kw", [dict(), dict(ta=True), dict(tb=True), dict(a_split=True), dict(f32=True, k_slices=2)])
+@pytest.mark.parametrize("tile,known", [(0, True), (64, True), (128, True), (77, False), (192, False), (-1, False), (64192, False), (32064, False)])
+def test_gemm_tile_selectors_that_a_caller_may_name(tile, known, kw):
+    """Only the header's selectors: the shapes that the library alone chooses fit fewer descriptors than those."""
+    kw = dict(kw)
+    f32 = kw.pop("f32", False)
+    op = gemm(104, 136, 264, tile=tile, **kw)
+    if f32:
+        op.flags |= B.F_OUT_F32
+    assert gemm_plan(op)[0] == (0 if known else B.EINVAL)
 
 
 def _declared_symbols():

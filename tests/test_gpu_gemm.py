@@ -403,6 +403,8 @@ def test_bad_arguments_are_refused_before_launch():
         B.gemm_op(None, a, c, 64, 64, 64),                   # null operand
         B.gemm_op(a.view(-1)[1:].data_ptr(), a, c, 8, 8, 8), # misaligned A
         B.gemm_op(a, a, c, 64, 64, 64, tile=77),             # unknown tile
+        B.gemm_op(a, a, c, 64, 64, 64, tile=64192),          # shapes that only the library chooses
+        B.gemm_op(a, a, c, 64, 64, 64, tile=32064),
         B.gemm_op(a, a, c, 64, 64, 64, tile=B.TILE_SKINNY),  # skinny needs M <= 32 and TRANS_B
     ]
     torch.cuda.synchronize()
