@@ -6,10 +6,10 @@
 //    layout: global memory straight into LDS, k-strided operands read with the
 //    transposing LDS load; the best-effort and training-shaped GEMMs;
 //  * gemm_lds256w8_kernel (gemm_lds256w8.hpp) - the same tiles by eight wavefronts, for an epilogue and element-wise stores;
-//  * gemm_mid_kernel (gemm_mid.hpp, gemm_tile128.hip, gemm_mid192.hip) - 128x128 and 64x192 tiles, any K % 8 == 0,
+//  * gemm_mid_kernel (gemm_mid.hpp, gemm_mid{128,192}.hip) - 128x128 and 64x192 tiles, any K % 8 == 0,
 //    split-bf16 A; global memory straight into LDS, three or four stages;
-//  * gemm_lds_kernel (gemm_lds.hpp, gemm_tile{64,128}.hip) - 64 tiles, any K % 8 == 0, split-bf16 A, and 128 tiles of two
-//    k-contiguous operands with a long K; global memory straight into LDS, two or three stages;
+//  * gemm_lds_kernel (gemm_lds.hpp, gemm_tile{64,128}.hip) - 64 tiles, any K % 8 == 0, split-bf16 A, and the 128 tiles that
+//    gemm_mid_kernel does not serve (see gemm_plan); global memory straight into LDS, two or three stages;
 //  * gemm_tile_kernel (gemm_tile.hpp, gemm_tile256_{wide,elem}.hip) - 256 tiles with any other K, through registers;
 //  * gemm_skinny_*_kernel (gemm_skinny.hip) - M <= 32 rows (bf16 or fp32
 //    activations) against a [N,K] bf16 weight matrix: HBM-bound, the weights are
@@ -29,28 +29,31 @@ namespace lithos {
 
 // ---- host side -------------------------------------------------------------
 
-// The 128, 64x192 and 256 tiles address their operands with 32-bit byte offsets from the tile's first row: 256 rows of this
-// many elements are 2 GiB.  Longer rows take the kernels with 64-bit addresses.
+// gemm_lds256_kernel, gemm_mid_kernel and gemm_thin_kernel address their operands with 32-bit byte offsets from the tile's
+// first row: 256 rows of this many elements are 2 GiB.  Longer rows take the same tiles, and choose among them, as the kernels
+// with 64-bit addresses do.
 constexpr int64_t MAX_OFFSET_LD = 1 << 22;
 
 // Tile shapes that auto_tile alone chooses.
 constexpr int TILE_64X192 = 64192, TILE_32X64 = 32064;
 
 // The tile of a GEMM that names none.
-static int auto_tile(int64_t M, int64_t N, bool split, bool sliced)
+static int auto_tile(int64_t M, int64_t N, bool split, bool sliced, bool long_rows)
 {
     const auto blocks = [&](int64_t bm, int64_t bn) { return ((M + bm - 1) / bm) * ((N + bn - 1) / bn); };
     // Split A (us, 64x192 / 128x128 / 64x64): 4096 x 2304 x 768 31.1 / 36.7 / 48, 4096 x 768 x 3072 35.9 / 43.2 / 57,
     // 4096 x 3072 x 768 39.3 / 38.4 / 62, 1024 x 2304 x 768 (192 blocks) 10.5 / 12.1 / 16.3; 64 blocks or fewer leave too
     // much of the chip idle: 1024 x 768 x 3072 31.6 / 40.2 / 21.3.
     // At most one 32x64 tile per CU of a quarter of the chip: see gemm_thin.hip.
-    if (split && !sliced && blocks(32, 64) <= 64) return TILE_32X64;
-    if (split) return blocks(64, 192) >= 128 ? TILE_64X192 : 64;
+    if (split && !long_rows) {
+        if (!sliced && blocks(32, 64) <= 64) return TILE_32X64;
+        return blocks(64, 192) >= 128 ? TILE_64X192 : 64;
+    }
     if (blocks(128, 128) < 128) return 64;
-    return blocks(256, 256) >= 256 ? 256 : 128;
+    return !split && blocks(256, 256) >= 256 ? 256 : 128;
 }
 
-static int tile_threads(int variant) { return variant == V_TILE64 || variant == V_TILE128 || variant == V_MID192 || variant == V_THIN || variant == V_TILE128_DEEP || variant == V_LDS256 ? 256 : 512; }
+static int tile_threads(int variant) { return variant == V_TILE64 || variant == V_TILE128 || variant == V_MID128 || variant == V_MID192 || variant == V_THIN || variant == V_LDS256 ? 256 : 512; }
 
 // full bf16 tiles can leave through LDS when whole 16-byte pieces of C rows are addressable
 // (fp32 tiles of the same kernels are stored from registers, 16 bytes per lane)
@@ -70,8 +73,8 @@ static gemm_fn variant_fn(int variant, bool ta, bool tb, bool a32, bool split, b
     case V_LDS256W8: return st ? gemm_lds256w8_wide_fn(ta, tb) : gemm_lds256w8_elem_fn(ta, tb);
     case V_TILE64: return gemm_tile64_fn(ta, tb, split, st, false);
     case V_TILE64_2K: return gemm_tile64_fn(ta, tb, split, st, true);
-    case V_TILE128: return gemm_tile128_fn(ta, tb, split);
-    case V_TILE128_DEEP: return gemm_tile128_deep_fn(st);
+    case V_TILE128: return gemm_tile128_fn(ta, tb, split, st);
+    case V_MID128: return gemm_mid128_fn(ta, tb, split);
     case V_THIN: return gemm_thin_fn(tb);
     case V_MID192: return gemm_mid192_fn(tb);
     case V_TILE256: return st ? gemm_tile256_wide_fn(ta, tb) : gemm_tile256_elem_fn(ta, tb);
@@ -114,6 +117,7 @@ int gemm_plan(const lithos_op_t& op, OpPlan* plan)
     }
     const int norm = norm_of(op.flags);
     const bool glu = op.flags & LITHOS_F_GLU, fused = norm || glu;
+    const bool long_rows = lda > MAX_OFFSET_LD || ldb > MAX_OFFSET_LD;
     int tile = op.tile;
     // What a caller may name.  The shapes that auto_tile alone chooses are built for fewer descriptors and not checked for below.
     if (tile != 0 && tile != LITHOS_TILE_SKINNY && tile != 64 && tile != 128 && tile != 256)
@@ -122,7 +126,7 @@ int gemm_plan(const lithos_op_t& op, OpPlan* plan)
         return fail(LITHOS_EINVAL, "gemm: fp32 activations (IN_F32) are only taken by the skinny kernel (M <= 32, TRANS_B)");
     if (tile == 0) {
         if (M <= 32 && tb && !ta && slices <= 1) tile = LITHOS_TILE_SKINNY;
-        else tile = auto_tile(M, N, split, slices > 1);
+        else tile = auto_tile(M, N, split, slices > 1, long_rows);
     }
     int variant;
     if (tile == LITHOS_TILE_SKINNY) {
@@ -149,9 +153,7 @@ int gemm_plan(const lithos_op_t& op, OpPlan* plan)
     } else {
         if (fused) return fail(LITHOS_EINVAL, "gemm: NORM_LN, NORM_RMS and GLU are built into the weight-streaming kernel only (TRANS_B, M <= 16)");
         if (split && tile == 256) return fail(LITHOS_EINVAL, "gemm: SPLIT_A is built for the 64 and 128 tiles only");
-        const bool long_rows = lda > MAX_OFFSET_LD || ldb > MAX_OFFSET_LD;
-        if (long_rows && tile != 256) tile = 64;
-        variant = tile == 64 ? V_TILE64 : tile == 128 ? V_TILE128 : tile == 256 ? V_TILE256 : tile == TILE_32X64 ? V_THIN : V_MID192;
+        variant = tile == 64 ? V_TILE64 : tile == 128 ? V_MID128 : tile == 256 ? V_TILE256 : tile == TILE_32X64 ? V_THIN : V_MID192;
         // Stores of single elements (a row or its last tile that does not divide into 16-byte pieces) are slower from the
         // layouts of the 16x16x32 kernels.
         const bool pieces = staged_epilogue(op) && N % 8 == 0;
@@ -162,7 +164,7 @@ int gemm_plan(const lithos_op_t& op, OpPlan* plan)
         // Both operands k-contiguous and K long: with several workgroups on a CU the half lines of 32-deep k-tiles cost more than
         // the rest of the kernel gains (us, 32 / 64 deep, on 64 CUs: 512 x 4096 x 4096 57 / 50, 200 x 6000 x 6000 113 / 90,
         // 2048^3 52 / 54; on 256 CUs 33 / 46, 62 / 75, 22 / 28).
-        if (variant == V_TILE128 && !split && !ta && tb && (K > 2048 || !pieces)) variant = V_TILE128_DEEP;
+        if (variant == V_MID128 && (long_rows || (!split && !ta && tb && (K > 2048 || !pieces)))) variant = V_TILE128;
         const int64_t bm = tile == TILE_64X192 ? 64 : tile == TILE_32X64 ? 32 : tile, bn = tile == TILE_64X192 ? 192 : tile == TILE_32X64 ? 64 : tile;
         plan->grid = {(uint32_t)((N + bn - 1) / bn), (uint32_t)((M + bm - 1) / bm), (uint32_t)(slices > 1 ? slices : 1)};
         // The 64 tile splits K between two groups of wavefronts while all blocks of the whole grid (never of an atom: the

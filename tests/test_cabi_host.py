@@ -59,6 +59,34 @@ def test_gemm_tile_selectors_that_a_caller_may_name(tile, known, kw):
     assert gemm_plan(op)[0] == (0 if known else B.EINVAL)
 
 
+# kernels by the plan's variant number (enum in gemm_common.hpp), workgroup size
+TILE64_2K, TILE128, MID128, LDS256, LDS256W8 = (11, 512), (20, 256), (21, 256), (31, 256), (32, 512)
+LONG = (1 << 22) + 8        # elements of a row beyond which 32-bit byte offsets within a tile would not do
+
+
+def _kernel(op):
+    rc, plan = gemm_plan(op)
+    assert rc == 0
+    return (plan.variant, plan.threads), tuple(plan.grid)
+
+
+@pytest.mark.parametrize("ta,tb,split", [(False, False, False), (False, True, False), (True, False, False), (True, True, False),
+                                         (False, False, True), (False, True, True)])
+@pytest.mark.parametrize("long", ["lda", "ldb"])
+def test_rows_beyond_32_bit_offsets_keep_the_named_tile(ta, tb, split, long):
+    """A named 128 or 256 tile is that tile whatever the length of the rows; from rows of more than 4M elements on a kernel
+    with 64-bit addresses computes it.  Without a named tile such a split A is cut into the square tiles."""
+    m, n, k = 304, 264, 64
+    for ld, tile128, tile256 in ((LONG - 8, MID128, LDS256), (LONG, TILE128, LDS256W8)):
+        kw = dict(ta=ta, tb=tb, a_split=split, **{long: ld})
+        assert _kernel(gemm(m, n, k, tile=128, **kw)) == (tile128, (3, 3, 1))
+        if not split:
+            assert _kernel(gemm(m, n, k, tile=256, **kw)) == (tile256, (2, 2, 1))
+    if split:
+        assert _kernel(gemm(m, n, k, **kw)) == (TILE64_2K, (5, 5, 1))
+        assert _kernel(gemm(2048, 2048, k, **kw)) == (TILE128, (16, 16, 1))
+
+
 def _declared_symbols():
     text = open(os.path.join(ROOT, "include", "lithos.h")).read()
     text = re.sub(r"/\*.*?\*/", "", text, flags=re.S)

@@ -855,15 +855,27 @@ def test_split_activations_in_tiles_chosen_by_size(m, n, k, tb, grid):
 
 
 @pytest.mark.parametrize("tile,split", [(64, False), (128, False), (256, False), (0, True), (64, True), (128, True)])
-def test_rows_longer_than_32_bit_offsets(tile, split):
-    """Rows of more than 4M elements take the kernels with 64-bit addresses, whatever tile is named."""
-    m, n, k, ld = 3, 72, 64, (1 << 22) + 8
-    a_bits, b_bits = inputs.normal_bits((m, k), 80), inputs.normal_bits((k, n), 81)
-    a = torch.zeros((2 if split else 1, m, ld), dtype=torch.bfloat16, device="cuda")
-    a[0, :, :k] = dev_bits(a_bits)
+@pytest.mark.parametrize("long,ta,tb", [("a", False, False), ("a", True, False), ("b", False, True), ("b", False, False)])
+@pytest.mark.parametrize("ld", [1 << 22, (1 << 22) + 8])
+def test_rows_longer_than_32_bit_offsets(tile, split, long, ta, tb, ld):
+    """Rows of 4M elements, the most that 32-bit byte offsets within a tile reach, and longer ones (64-bit addresses), of
+    either operand: the last row of the first tile lies up to 2 GiB behind its first.  NaN fills what lies between the rows."""
+    if split and ta:
+        ta, tb = False, True                    # a split A is not transposed: its planes beside a k-contiguous B
+    m, n, k = 272, 264, 64
+    a_bits, b_bits = inputs.gemm_operands(m, n, k, seed=80 + tile, ta=ta, tb=tb)
+    ref = O.gemm(a_bits, b_bits, ta=ta, tb=tb)
+    lda, ldb = (ld, b_bits.shape[1]) if long == "a" else (a_bits.shape[1], ld)
+
+    def strided(bits, cols):
+        t = nan_like((bits.shape[0], cols), torch.bfloat16)
+        t[:, :bits.shape[1]] = dev_bits(bits)
+        return t
+    a, b = strided(a_bits, lda), strided(b_bits, ldb)
+    if split:                                   # lo plane = hi plane scaled by 2^-8: exactly representable
+        a = torch.stack([a, a])
+        a[1, :, :k] *= 2.0 ** -8
+        ref = ref * (1.0 + 2.0 ** -8)
     c = nan_like((m, n), torch.float32)
-    torch.cuda.synchronize()
-    op = B.gemm_op(a, dev_bits(b_bits), c, m, n, k, lda=ld, tile=tile, a_split=split)
-    B.lithos_launch_atomized(ctx(), op)
-    B.lithos_partition_sync(ctx(), None)
-    assert rel_fro(c, O.gemm(a_bits, b_bits)) <= 1e-6
+    _launch(B.gemm_op(a, b, c, m, n, k, ta=ta, tb=tb, lda=lda, ldb=ldb, tile=tile, a_split=split))
+    assert rel_fro(c, ref) <= 1e-6
