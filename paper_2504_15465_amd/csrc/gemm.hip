@@ -53,7 +53,7 @@ static int auto_tile(int64_t M, int64_t N, bool split, bool sliced, bool long_ro
     return !split && blocks(256, 256) >= 256 ? 256 : 128;
 }
 
-static int tile_threads(int variant) { return variant == V_TILE64 || variant == V_TILE128 || variant == V_MID128 || variant == V_MID192 || variant == V_THIN || variant == V_LDS256 ? 256 : 512; }
+static int tile_threads(int variant) { return variant == V_TILE64 || variant == V_TILE128 || variant == V_MID128 || variant == V_MID128_PAIR || variant == V_MID192 || variant == V_THIN || variant == V_LDS256 ? 256 : 512; }
 
 // full bf16 tiles can leave through LDS when whole 16-byte pieces of C rows are addressable
 // (fp32 tiles of the same kernels are stored from registers, 16 bytes per lane)
@@ -76,6 +76,7 @@ static gemm_fn variant_fn(int variant, bool ta, bool tb, bool a32, bool split, b
     case V_TILE128: return gemm_tile128_fn(ta, tb, split, st);
     case V_MID128: return gemm_mid128_fn(ta, tb, split);
     case V_THIN: return gemm_thin_fn(tb);
+    case V_MID128_PAIR: return gemm_mid128_pair_fn(ta, tb);
     case V_MID192: return gemm_mid192_fn(tb);
     case V_TILE256: return st ? gemm_tile256_wide_fn(ta, tb) : gemm_tile256_elem_fn(ta, tb);
     default: return gemm_skinny_fn(variant, a32, norm);
@@ -153,7 +154,7 @@ int gemm_plan(const lithos_op_t& op, OpPlan* plan)
     } else {
         if (fused) return fail(LITHOS_EINVAL, "gemm: NORM_LN, NORM_RMS and GLU are built into the weight-streaming kernel only (TRANS_B, M <= 16)");
         if (split && tile == 256) return fail(LITHOS_EINVAL, "gemm: SPLIT_A is built for the 64 and 128 tiles only");
-        variant = tile == 64 ? V_TILE64 : tile == 128 ? V_MID128 : tile == 256 ? V_TILE256 : tile == TILE_32X64 ? V_THIN : V_MID192;
+        variant = tile == 64 ? V_TILE64 : tile == 256 ? V_TILE256 : tile == TILE_32X64 ? V_THIN : V_MID192;     // 128: below
         // Stores of single elements (a row or its last tile that does not divide into 16-byte pieces) are slower from the
         // layouts of the 16x16x32 kernels.
         const bool pieces = staged_epilogue(op) && N % 8 == 0;
@@ -161,10 +162,20 @@ int gemm_plan(const lithos_op_t& op, OpPlan* plan)
         // eight wavefronts: 2048 x 2048 x 512 with bias 24 / 18, with residual too 36 / 25, with GELU too 47 / 31; 4096 x 4096 x 1024 with
         // bias and residual 55 / 44; with all three 4096 x 8192 x 4096 284 / 265, 256 x 256 x 8192 167 / 165).
         if (tile == 256 && K % 64 == 0) variant = long_rows || !pieces || (op.flags & (LITHOS_F_BIAS | LITHOS_F_GELU | LITHOS_F_RESIDUAL)) ? V_LDS256W8 : V_LDS256;
-        // Both operands k-contiguous and K long: with several workgroups on a CU the half lines of 32-deep k-tiles cost more than
-        // the rest of the kernel gains (us, 32 / 64 deep, on 64 CUs: 512 x 4096 x 4096 57 / 50, 200 x 6000 x 6000 113 / 90,
-        // 2048^3 52 / 54; on 256 CUs 33 / 46, 62 / 75, 22 / 28).
-        if (variant == V_MID128 && (long_rows || (!split && !ta && tb && (K > 2048 || !pieces)))) variant = V_TILE128;
+        if (tile == 128) {
+            // V_MID128's k-tiles are 32 deep: 64 bytes, half a line, of a row of a k-contiguous operand.  With several workgroups on a CU
+            // the line has left the L1 when its other half is fetched, a k-tile later.  V_MID128_PAIR fetches both halves in one turn,
+            // which costs 0.3 us and pays from 512 of K on, where rows do not begin on lines (a half then touches two) from 256 (us,
+            // single / in pairs: 1024 x 1024 x 256 NT on 64 CUs 5.4 / 5.7, 2048 x 2048 x 1544 on 256 24.0 / 21.2, x 2040 on 192 48 / 41).
+            // V_TILE128's are 64 deep and touch half the lines per load: better for two such operands with more than a tile per CU and
+            // a long K (in pairs / 64 deep: 3000 x 2048 x 1544 on 192 CUs 35.3 / 32.0, 8192 x 512 x 5000 on 64 194 / 165, but
+            // 2048 x 2048 x 1544 on 256 21.2 / 27.3, 512 x 1024 x 4096 on 64 28 / 45).
+            const int64_t tiles = ((M + 127) / 128) * ((N + 127) / 128);
+            const bool lines = (ta || lda % 64 == 0) && (!tb || ldb % 64 == 0), nt = !ta && tb;
+            const bool pair = !split && (!ta || tb) && K > (lines ? 512 : 256);
+            const bool deep = !split && nt && (!pieces || (K > 2048 ? tiles > 64 : !lines && K > 1280 && tiles > 256));
+            variant = long_rows || deep ? V_TILE128 : pair ? V_MID128_PAIR : V_MID128;
+        }
         const int64_t bm = tile == TILE_64X192 ? 64 : tile == TILE_32X64 ? 32 : tile, bn = tile == TILE_64X192 ? 192 : tile == TILE_32X64 ? 64 : tile;
         plan->grid = {(uint32_t)((N + bn - 1) / bn), (uint32_t)((M + bm - 1) / bm), (uint32_t)(slices > 1 ? slices : 1)};
         // The 64 tile splits K between two groups of wavefronts while all blocks of the whole grid (never of an atom: the

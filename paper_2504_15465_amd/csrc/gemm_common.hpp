@@ -248,6 +248,7 @@ typedef void (*gemm_fn)(GemmArgs, AtomArgs);
 gemm_fn gemm_tile64_fn(bool ta, bool tb, bool split, bool st, bool two_groups);
 gemm_fn gemm_tile128_fn(bool ta, bool tb, bool split, bool st);
 gemm_fn gemm_mid128_fn(bool ta, bool tb, bool split);
+gemm_fn gemm_mid128_pair_fn(bool ta, bool tb);
 gemm_fn gemm_mid192_fn(bool tb);
 gemm_fn gemm_thin_fn(bool tb);
 gemm_fn gemm_tile256_wide_fn(bool ta, bool tb);
@@ -261,7 +262,7 @@ gemm_fn gemm_skinny_fn(int variant, bool a32, int norm);
 constexpr int SKINNY_WAVES = 8;     // wavefronts per workgroup of the skinny kernels, each owning one slice of K
 constexpr int SKINNY_NB = 2;        // 16-column blocks per workgroup of the skinny kernels
 
-enum { V_SKINNY32 = 3, V_TILE64 = 10, V_TILE64_2K = 11, V_TILE128 = 20, V_MID128 = 21, V_MID192 = 22, V_THIN = 23, V_TILE256 = 30, V_LDS256 = 31, V_LDS256W8 = 32,
+enum { V_SKINNY32 = 3, V_TILE64 = 10, V_TILE64_2K = 11, V_TILE128 = 20, V_MID128 = 21, V_MID128_PAIR = 22, V_MID192 = 23, V_THIN = 24, V_TILE256 = 30, V_LDS256 = 31, V_LDS256W8 = 32,
        V_SKL4 = 40, V_SKL8 = 41, V_SKL16 = 42 };   // 2K: two groups of wavefronts split K; SKL: LDS-staged activations of at most 4 / 8 / 16 rows
 
 } // namespace lithos

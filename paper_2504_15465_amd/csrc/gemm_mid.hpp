@@ -10,6 +10,10 @@ namespace lithos {
 // grids here too (4096 x 2304 x 768 split: MFMA pipes 80 % busy at 1.73 GHz), the number of tiles that the busiest CU gets
 // the smaller ones: a split A, whose N are multiples of 192 in the encoder, takes 64x192 (768 tiles for 4096 x 2304, three to a CU).
 //
+// S = 5: two k-tiles at a time, every second turn, so that both halves of a line of a k-contiguous operand are fetched one after the
+// other and the second comes from the L1.  A k-tile late: with two workgroups per CU the line is gone by then (K <= 2048, NT,
+// rows that do not begin on lines, more than two tiles per CU: 0.80 to 0.97 of the time of S = 4; see gemm_plan).
+//
 // Against 32x32x16 MFMAs whose loads took five vector instructions each (us): 2048^3 NN 30 -> 21, 1536 x 1536 x 8192 TN 88 ->
 // 51, 1003 x 3000 x 1160 NT with epilogue 26.5 -> 23, split 4096 x 2304 x 768 41 -> 31, 4096 x 768 x 3072 55 -> 39.
 template <int BM, int BN, int WGM, int WGN, int S, int MINW, bool KSA, bool KSB, bool SPLIT>
@@ -18,6 +22,7 @@ void gemm_mid_kernel(GemmArgs g, AtomArgs atom)
 {
 #ifdef __HIP_DEVICE_COMPILE__       // the buffer types exist on the device only
     static_assert(WGM * WGN == 4 && S >= 3 && S <= 5, "built forms");
+    constexpr bool PAIR = S == 5;                                        // k-tiles are fetched two at a time
     constexpr int BK = 32, WM = BM / WGM, WN = BN / WGN, MI = WM / 16, NI = WN / 16, AP = SPLIT ? 2 : 1;
     constexpr int NF = AP * MI + NI, NM = AP * MI * NI;                  // fragments and MFMAs of a k-tile
     constexpr int TA = BM / 16, TB = BN / 16;                            // 1 KB blocks of an operand's k-tile
@@ -94,21 +99,32 @@ void gemm_mid_kernel(GemmArgs g, AtomArgs atom)
     // k beyond the block's range must arrive as zeros.  k-strided: the buffer ends behind the last k-row.  k-contiguous:
     // the lanes whose chunk lies beyond get an offset that no buffer holds (all of them behind the last tile).
     const int lane_k = ((lane & 7) ^ (lane >> 3)) % 4 * 8;
-    const auto load = [&](auto qc, uint16_t* At, uint16_t* Bt) __attribute__((always_inline)) {
-        constexpr int q = decltype(qc)::value;
-        const int left = __builtin_amdgcn_readfirstlane(max(to_fetch, 0));
-        const uint32_t beyond = lane_k < to_fetch ? 0u : ~0u;
+    // Load q of the d-th of the k-tiles that are not yet fetched, and then to the tiles behind them.
+    const auto load = [&](auto qc, auto dc, uint16_t* At, uint16_t* Bt) __attribute__((always_inline)) {
+        constexpr int q = decltype(qc)::value, d = decltype(dc)::value;
+        const int left = __builtin_amdgcn_readfirstlane(max(to_fetch - d * BK, 0));
+        const uint32_t beyond = lane_k < to_fetch - d * BK ? 0u : ~0u;
         const auto rsrc = [&](auto ks, const uint16_t* p, int64_t ld) __attribute__((always_inline)) {
             return __builtin_amdgcn_make_buffer_rsrc((void*)p, 0, decltype(ks)::value ? min(left, BK) * (int)ld * 2 : -1, 0x00020000);
         };
         if constexpr (q < NB) {
-            __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc(ksb, pb, g.ldb), (lptr_t)(Bt + b_block(q) * 512), 16, KSB ? ob[q] : ob[q] | beyond, 0, 0, 0);
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc(ksb, pb + d * b_step, g.ldb), (lptr_t)(Bt + b_block(q) * 512), 16, KSB ? ob[q] : ob[q] | beyond, 0, 0, 0);
         } else {
             constexpr int i = (q - NB) / AP, p = (q - NB) % AP;
-            __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc(ksa, SPLIT ? pa + p * g.a_plane : pa, g.lda), (lptr_t)(At + p * (BM * BK) + (wave * NA + i) * 512), 16,
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc(ksa, (SPLIT ? pa + p * g.a_plane : pa) + d * a_step, g.lda), (lptr_t)(At + p * (BM * BK) + (wave * NA + i) * 512), 16,
                                                      KSA ? oa[i] : oa[i] | beyond, 0, 0, 0);
         }
-        if constexpr (q == NL - 1) { to_fetch -= BK; pa += a_step; pb += b_step; }
+    };
+    const auto fetched = [&](int tiles) __attribute__((always_inline)) { to_fetch -= tiles * BK; pa += tiles * a_step; pb += tiles * b_step; };
+    // Loads i0 .. i1 - 1 of k-tile t, or of the pair t, t + 1, the same block of both one after the other.
+    const auto load_range = [&](auto tc, auto i0c, auto i1c) __attribute__((always_inline)) {
+        constexpr int t = decltype(tc)::value, i0 = decltype(i0c)::value, i1 = decltype(i1c)::value, N = PAIR ? 2 : 1;
+        static_for<i1 - i0>([&](auto ic) __attribute__((always_inline)) {
+            constexpr int i = i0 + decltype(ic)::value;
+            constexpr std::integral_constant<int, t + i % N> tile{};
+            load(std::integral_constant<int, i / N>{}, std::integral_constant<int, i % N>{}, stage_a(tile), stage_b(tile));
+        });
+        if constexpr (i1 > i0 && i1 == N * NL) fetched(N);
     };
 
     // Where this lane reads in a stage: a fragment is 16 rows, this lane row l16, the 8 k of chunk `quad`.  k-strided:
@@ -169,9 +185,11 @@ void gemm_mid_kernel(GemmArgs g, AtomArgs atom)
     constexpr int RS = NM * 3 / 4;                  // MFMAs that are followed by the reads of the next tile
     const auto tile_step = [&](auto tc) __attribute__((always_inline)) {
         constexpr int t = decltype(tc)::value;
-        constexpr std::integral_constant<int, t> cur{};
         constexpr std::integral_constant<int, t + 1> next{};
-        turn(std::integral_constant<int, (S - 2) * NL>{});
+        constexpr int F = !PAIR ? NL : t % 2 == 0 ? 2 * NL : 0;     // loads to issue: tile t + S, or the pair t + 4, t + 5
+        // May still be in flight, tile t + 1 having landed: the S - 2 tiles behind it; the pair behind its own and, where it is the
+        // first of its own, that pair's last load.
+        turn(std::integral_constant<int, !PAIR ? (S - 2) * NL : 2 * NL + t % 2>{});
         static_for<NM>([&](auto mc) __attribute__((always_inline)) {
             // the small plane of a split A first; operands exchanged: a lane then holds four consecutive columns of one row of C
             constexpr int m = decltype(mc)::value, p = AP - 1 - m / (MI * NI), i = m % (MI * NI) / NI, j = m % NI;
@@ -182,14 +200,16 @@ void gemm_mid_kernel(GemmArgs g, AtomArgs atom)
                     read(std::integral_constant<int, r0 + decltype(r)::value>{}, stage_a(next), stage_b(next), std::integral_constant<int, (t + 1) & 1>{});
                 });
             }
-            constexpr int l0 = m * NL / NM, l1 = (m + 1) * NL / NM;
-            static_for<l1 - l0>([&](auto l) __attribute__((always_inline)) { load(std::integral_constant<int, l0 + decltype(l)::value>{}, stage_a(cur), stage_b(cur)); });
+            load_range(std::integral_constant<int, PAIR ? t + 4 : t + S>{}, std::integral_constant<int, m * F / NM>{}, std::integral_constant<int, (m + 1) * F / NM>{});
             __builtin_amdgcn_sched_barrier(0);
         });
     };
 
-    static_for<S>([&](auto s) __attribute__((always_inline)) { static_for<NL>([&](auto q) __attribute__((always_inline)) { load(q, stage_a(s), stage_b(s)); }); });
-    turn(std::integral_constant<int, (S - 1) * NL>{});
+    constexpr int G = PAIR ? 2 : 1;                 // tiles that are fetched together
+    static_for<PAIR ? 2 : S>([&](auto f) __attribute__((always_inline)) {
+        load_range(std::integral_constant<int, decltype(f)::value * G>{}, std::integral_constant<int, 0>{}, std::integral_constant<int, G * NL>{});
+    });
+    turn(std::integral_constant<int, PAIR ? 2 * NL + 1 : (S - 1) * NL>{});      // tile 0 has landed
     static_for<NF>([&](auto q) __attribute__((always_inline)) { read(q, A0, B0, std::integral_constant<int, 0>{}); });
     // whole rounds of the stages and fragment sets, then the rest
     constexpr int U = S % 2 ? 2 * S : S;

@@ -60,7 +60,7 @@ def test_gemm_tile_selectors_that_a_caller_may_name(tile, known, kw):
 
 
 # kernels by the plan's variant number (enum in gemm_common.hpp), workgroup size
-TILE64_2K, TILE128, MID128, LDS256, LDS256W8 = (11, 512), (20, 256), (21, 256), (31, 256), (32, 512)
+TILE64_2K, TILE128, MID128, MID128_PAIR, LDS256, LDS256W8 = (11, 512), (20, 256), (21, 256), (22, 256), (31, 256), (32, 512)
 LONG = (1 << 22) + 8        # elements of a row beyond which 32-bit byte offsets within a tile would not do
 
 
@@ -85,6 +85,20 @@ def test_rows_beyond_32_bit_offsets_keep_the_named_tile(ta, tb, split, long):
     if split:
         assert _kernel(gemm(m, n, k, **kw)) == (TILE64_2K, (5, 5, 1))
         assert _kernel(gemm(2048, 2048, k, **kw)) == (TILE128, (16, 16, 1))
+
+
+@pytest.mark.parametrize("ta,tb,m,n,k,pad,kernel", [
+    (False, True, 2048, 2048, 256, 8, MID128), (False, True, 2048, 2048, 264, 0, MID128_PAIR),      # rows beside lines: pairs from 256 on
+    (False, True, 2048, 2048, 512, 0, MID128), (False, True, 2048, 2048, 576, 0, MID128_PAIR),      # rows on lines: from 512 on
+    (False, False, 2048, 2048, 512, 0, MID128), (False, False, 2048, 2048, 520, 0, MID128_PAIR),
+    (True, True, 2048, 2048, 512, 8, MID128_PAIR), (True, False, 2048, 2048, 2048, 8, MID128),      # k-strided rows do not count
+    (False, True, 2048, 2048, 1544, 0, MID128_PAIR), (False, True, 2176, 2048, 1544, 0, TILE128),   # more than 256 tiles
+    (False, True, 2176, 2048, 1280, 8, MID128_PAIR), (False, True, 2176, 2048, 1536, 0, MID128_PAIR),
+    (False, True, 1024, 1024, 2112, 0, MID128_PAIR), (False, True, 1024, 1152, 2112, 0, TILE128),   # more than 64 tiles
+    (False, False, 4096, 4096, 8192, 8, MID128_PAIR),
+])
+def test_depth_of_the_128_tiles_k_tiles(ta, tb, m, n, k, pad, kernel):
+    assert _kernel(gemm(m, n, k, ta=ta, tb=tb, tile=128, lda=(m if ta else k) + pad, ldb=(k if tb else n) + pad))[0] == kernel
 
 
 def _declared_symbols():

@@ -879,3 +879,21 @@ def test_rows_longer_than_32_bit_offsets(tile, split, long, ta, tb, ld):
     c = nan_like((m, n), torch.float32)
     _launch(B.gemm_op(a, b, c, m, n, k, ta=ta, tb=tb, lda=lda, ldb=ldb, tile=tile, a_split=split))
     assert rel_fro(c, ref) <= 1e-6
+
+
+@pytest.mark.parametrize("ta,tb", [(False, True), (False, False), (True, True)])
+@pytest.mark.parametrize("k,slices", [(264, 0), (520, 0), (576, 0), (640, 0), (680, 0), (776, 3), (1000, 0)])
+def test_k_tiles_fetched_in_pairs(ta, tb, k, slices):
+    """128 tiles with a k-contiguous operand and 9 to 32 k-tiles of 32, even and odd numbers of them and a last one of 8, in rows that
+    begin on lines and rows that do not; operands inside larger buffers of NaN; K slices with uneven cuts.
+    fp32 sums: at most K * 2^-24 of the sum of magnitudes (K / 4 for uniform operands)."""
+    m, n = 136, 152
+    a_bits, b_bits = inputs.gemm_operands(m, n, k, seed=k, ta=ta, tb=tb)
+    ref = O.gemm(a_bits, b_bits, ta=ta, tb=tb)
+    bound = 2.0 ** -24 * k * (k / 4 + 1)
+    for odd in (8, 0):                          # row strides beside multiples of 64, and multiples
+        lda, ldb = ((b.shape[1] + 63) // 64 * 64 + odd for b in (a_bits, b_bits))
+        a, b = _padded(a_bits, lda), _padded(b_bits, ldb)
+        c = nan_like((max(slices, 1), m, n), torch.float32)
+        _launch(B.gemm_op(a, b, c, m, n, k, ta=ta, tb=tb, tile=128, lda=lda, ldb=ldb, k_slices=slices), 3)
+        assert np.abs(c.double().sum(0).cpu().numpy() - ref).max() <= bound
