@@ -155,9 +155,7 @@ int gemm_plan(const lithos_op_t& op, OpPlan* plan)
         if (fused) return fail(LITHOS_EINVAL, "gemm: NORM_LN, NORM_RMS and GLU are built into the weight-streaming kernel only (TRANS_B, M <= 16)");
         if (split && tile == 256) return fail(LITHOS_EINVAL, "gemm: SPLIT_A is built for the 64 and 128 tiles only");
         variant = tile == 64 ? V_TILE64 : tile == 256 ? V_TILE256 : tile == TILE_32X64 ? V_THIN : V_MID192;     // 128: below
-        // Stores of single elements (a row or its last tile that does not divide into 16-byte pieces) are slower from the
-        // layouts of the 16x16x32 kernels.
-        const bool pieces = staged_epilogue(op) && N % 8 == 0;
+        const bool pieces = staged_epilogue(op) && N % 8 == 0;      // every row of C leaves in 16-byte pieces
         // Four wavefronts gain 15 % in the loop and lose in an epilogue, 5 us a tile with bias and residual and 13 with GELU (us, four /
         // eight wavefronts: 2048 x 2048 x 512 with bias 24 / 18, with residual too 36 / 25, with GELU too 47 / 31; 4096 x 4096 x 1024 with
         // bias and residual 55 / 44; with all three 4096 x 8192 x 4096 284 / 265, 256 x 256 x 8192 167 / 165).
@@ -173,7 +171,7 @@ int gemm_plan(const lithos_op_t& op, OpPlan* plan)
             const int64_t tiles = ((M + 127) / 128) * ((N + 127) / 128);
             const bool lines = (ta || lda % 64 == 0) && (!tb || ldb % 64 == 0), nt = !ta && tb;
             const bool pair = !split && (!ta || tb) && K > (lines ? 512 : 256);
-            const bool deep = !split && nt && (!pieces || (K > 2048 ? tiles > 64 : !lines && K > 1280 && tiles > 256));
+            const bool deep = !split && nt && (K > 2048 ? tiles > 64 : !lines && K > 1280 && tiles > 256);
             variant = long_rows || deep ? V_TILE128 : pair ? V_MID128_PAIR : V_MID128;
         }
         const int64_t bm = tile == TILE_64X192 ? 64 : tile == TILE_32X64 ? 32 : tile, bn = tile == TILE_64X192 ? 192 : tile == TILE_32X64 ? 64 : tile;

@@ -897,3 +897,40 @@ def test_k_tiles_fetched_in_pairs(ta, tb, k, slices):
         c = nan_like((max(slices, 1), m, n), torch.float32)
         _launch(B.gemm_op(a, b, c, m, n, k, ta=ta, tb=tb, tile=128, lda=lda, ldb=ldb, k_slices=slices), 3)
         assert np.abs(c.double().sum(0).cpu().numpy() - ref).max() <= bound
+
+
+@pytest.mark.parametrize("tile,ta,tb,split,k", [
+    (128, False, False, False, 72), (128, True, False, False, 72), (128, True, True, False, 328), (128, False, False, False, 328),
+    (128, False, True, False, 328), (128, False, False, True, 72), (0, False, False, True, 72), (0, False, True, True, 200),
+    (256, False, False, False, 64), (256, True, False, False, 192), (256, False, True, False, 64), (256, True, True, False, 192),
+])
+def test_rows_without_wide_stores_in_every_layout(tile, ta, tb, split, k):
+    """N a multiple of 8 in rows of C that no 16-byte piece fits (an odd stride, or an address beside 16 bytes): fp32, bf16 and paired
+    bf16 C, with bias, GELU and residual (its rows unaligned, too) and without, around the last row and column of a tile.
+    Error of the fp32 sum at most K * 2^-24 of the sum of magnitudes (K / 4 for uniform operands), GELU steepens it by at most 1.13."""
+    m, n = (1416, 1160) if tile == 0 else (tile + 8, tile + 24)     # 0: 161 tiles of 64x192
+    a_bits, b_bits = inputs.gemm_operands(m, n, k, seed=tile + k, ta=ta, tb=tb)
+    a, b = dev_bits(a_bits), dev_bits(b_bits)
+    acc = O.gemm(a_bits, b_bits, ta=ta, tb=tb)
+    if split:       # lo plane = hi plane scaled by 2^-8: exactly representable
+        a = torch.stack([a, (a.float() * 2.0 ** -8).to(torch.bfloat16)]).contiguous()
+        acc = acc * (1.0 + 2.0 ** -8)
+    pad = torch.randn(n + 1 + m * (n + 1) + 1, device="cuda")
+    bias, resid = pad[1:n + 1], pad[n + 2:].view(m, n + 1)[:, :n]
+    full = O.bias_act(acc, bias.double().cpu().numpy(), gelu=True) + resid.double().cpu().numpy()
+    bound = 1.13 * (2.0 ** -24 * k * (k / 4 + 1) + 2.0 ** -19)
+    for epi, ref in ((dict(), acc), (dict(bias=bias, gelu=True, residual=resid, ldr=n + 1), full)):
+        for dt, pair, ldc, first in ((torch.float32, False, n + 1, 0), (torch.bfloat16, False, n + 3, 0), (torch.bfloat16, False, n + 8, 1),
+                                     (torch.bfloat16, True, n + 4, 0)):
+            buf = nan_like(((2 if pair else 1) * m * ldc + first,), dt)
+            c = buf[first:].view(-1, m, ldc)
+            _launch(B.gemm_op(a, b, c, m, n, k, ta=ta, tb=tb, tile=tile, a_split=split, c_split=pair, ldc=ldc, **epi), 2)
+            assert torch.isnan(c[:, :, n:].float()).all() and not torch.isnan(c[:, :, :n].float()).any()
+            got = c[0, :, :n]
+            if dt is torch.float32:
+                assert np.abs(got.double().cpu().numpy() - ref).max() <= bound
+            else:
+                bf16_close(got, ref, abs_tol=bound)
+                if pair:
+                    both = got.double() + c[1, :, :n].double()
+                    assert np.abs(both.cpu().numpy() - ref).max() <= 2.0 ** -16 * np.abs(ref).max() + bound
