@@ -37,19 +37,26 @@ constexpr int64_t MAX_OFFSET_LD = 1 << 22;
 // Tile shapes that auto_tile alone chooses.
 constexpr int TILE_64X192 = 64192, TILE_32X64 = 32064;
 
-// The tile of a GEMM that names none.
-static int auto_tile(int64_t M, int64_t N, bool split, bool sliced, bool long_rows)
+// The tile of a GEMM that names none.  lines: rows of its k-contiguous operands begin on 128-byte lines.
+static int auto_tile(int64_t M, int64_t N, bool tb, bool split, bool sliced, bool long_rows, bool lines)
 {
     const auto blocks = [&](int64_t bm, int64_t bn) { return ((M + bm - 1) / bm) * ((N + bn - 1) / bn); };
-    // Split A (us, 64x192 / 128x128 / 64x64): 4096 x 2304 x 768 31.1 / 36.7 / 48, 4096 x 768 x 3072 35.9 / 43.2 / 57,
-    // 4096 x 3072 x 768 39.3 / 38.4 / 62, 1024 x 2304 x 768 (192 blocks) 10.5 / 12.1 / 16.3; 64 blocks or fewer leave too
-    // much of the chip idle: 1024 x 768 x 3072 31.6 / 40.2 / 21.3.
-    // At most one 32x64 tile per CU of a quarter of the chip: see gemm_thin.hip.
+    const auto rounds = [](int64_t blocks) { return (blocks + 255) / 256; };       // tiles of the busiest CU of the whole chip
+    const int64_t n128 = blocks(128, 128);
     if (split && !long_rows) {
+        // At most one 32x64 tile per CU of a quarter of the chip: see gemm_thin.hip.
         if (!sliced && blocks(32, 64) <= 64) return TILE_32X64;
-        return blocks(64, 192) >= 128 ? TILE_64X192 : 64;
+        // 64x192 tiles, if there is at least one for every second CU.  With few 128x128 tiles the choice is between them and 64x64
+        // tiles, which win while every CU has one at most (us, 64x192 / 64x64: 4096 x 256 x 768 10.2 / 7.7, 8192 x 128 x 3072 32 / 23;
+        // 4096 x 320 x 3072 on 128 CUs 38 / 53, 2048 x 768 x 768 NT on 64 18 / 27).
+        const int64_t n64 = blocks(64, 64), n192 = blocks(64, 192);
+        if (n128 < 128) return n192 >= 128 && n64 > 256 ? TILE_64X192 : 64;
+        // Else against 128x128, by the area of the busiest CU's tiles and of all (us, 64x192 / 128x128: 4096 x 768 x 3072 36 / 43, 4096 x
+        // 2304 x 768 31 / 37; 1500 x 2304 x 3072 62 / 47, 8192 x 256 x 768 on 64 CUs 35 / 27); not with half lines of two operands, of
+        // which the narrower tile fetches more (2048 x 2048 x 2056 NT 66 / 50).
+        return (lines || !tb) && rounds(n192) * 3 < rounds(n128) * 4 && n192 * 3 <= n128 * 4 ? TILE_64X192 : 128;
     }
-    if (blocks(128, 128) < 128) return 64;
+    if (n128 < 128) return 64;
     return !split && blocks(256, 256) >= 256 ? 256 : 128;
 }
 
@@ -119,6 +126,7 @@ int gemm_plan(const lithos_op_t& op, OpPlan* plan)
     const int norm = norm_of(op.flags);
     const bool glu = op.flags & LITHOS_F_GLU, fused = norm || glu;
     const bool long_rows = lda > MAX_OFFSET_LD || ldb > MAX_OFFSET_LD;
+    const bool lines = (ta || lda % 64 == 0) && (!tb || ldb % 64 == 0);     // rows of the k-contiguous operands begin on 128-byte lines
     int tile = op.tile;
     // What a caller may name.  The shapes that auto_tile alone chooses are built for fewer descriptors and not checked for below.
     if (tile != 0 && tile != LITHOS_TILE_SKINNY && tile != 64 && tile != 128 && tile != 256)
@@ -127,7 +135,7 @@ int gemm_plan(const lithos_op_t& op, OpPlan* plan)
         return fail(LITHOS_EINVAL, "gemm: fp32 activations (IN_F32) are only taken by the skinny kernel (M <= 32, TRANS_B)");
     if (tile == 0) {
         if (M <= 32 && tb && !ta && slices <= 1) tile = LITHOS_TILE_SKINNY;
-        else tile = auto_tile(M, N, split, slices > 1, long_rows);
+        else tile = auto_tile(M, N, tb, split, slices > 1, long_rows, lines);
     }
     int variant;
     if (tile == LITHOS_TILE_SKINNY) {
@@ -169,7 +177,7 @@ int gemm_plan(const lithos_op_t& op, OpPlan* plan)
             // a long K (in pairs / 64 deep: 3000 x 2048 x 1544 on 192 CUs 35.3 / 32.0, 8192 x 512 x 5000 on 64 194 / 165, but
             // 2048 x 2048 x 1544 on 256 21.2 / 27.3, 512 x 1024 x 4096 on 64 28 / 45).
             const int64_t tiles = ((M + 127) / 128) * ((N + 127) / 128);
-            const bool lines = (ta || lda % 64 == 0) && (!tb || ldb % 64 == 0), nt = !ta && tb;
+            const bool nt = !ta && tb;
             const bool pair = !split && (!ta || tb) && K > (lines ? 512 : 256);
             const bool deep = !split && nt && (K > 2048 ? tiles > 64 : !lines && K > 1280 && tiles > 256);
             variant = long_rows || deep ? V_TILE128 : pair ? V_MID128_PAIR : V_MID128;

@@ -101,6 +101,21 @@ def test_depth_of_the_128_tiles_k_tiles(ta, tb, m, n, k, pad, kernel):
     assert _kernel(gemm(m, n, k, ta=ta, tb=tb, tile=128, lda=(m if ta else k) + pad, ldb=(k if tb else n) + pad))[0] == kernel
 
 
+@pytest.mark.parametrize("m,n,k,tb,grid", [
+    (128, 768, 768, False, (12, 4)),            # at most 64 tiles of 32x64
+    (4096, 256, 768, False, (4, 64)),           # 256 tiles of 64x64, one per CU
+    (2048, 768, 768, False, (4, 32)),           # 384 of them: 128 of 64x192
+    (4096, 768, 3072, False, (4, 64)),          # 256 of 64x192, one round, against 192 of 128x128
+    (4096, 2304, 768, True, (12, 64)),
+    (4096, 3072, 768, False, (24, 32)),         # as much area on the busiest CU: 128x128
+    (1536, 2304, 768, False, (18, 12)),         # 288 of 64x192, two rounds, against 216 of 128x128
+    (8192, 256, 768, False, (2, 64)),           # a third of 64x192 tiles' columns would be padding
+    (4096, 768, 776, False, (4, 64)), (4096, 768, 776, True, (6, 32)),      # two operands whose rows do not begin on lines
+])
+def test_tile_of_a_split_gemm_that_names_none(m, n, k, tb, grid):
+    assert _kernel(gemm(m, n, k, tb=tb, a_split=True))[1] == grid + (1,)
+
+
 def _declared_symbols():
     text = open(os.path.join(ROOT, "include", "lithos.h")).read()
     text = re.sub(r"/\*.*?\*/", "", text, flags=re.S)
