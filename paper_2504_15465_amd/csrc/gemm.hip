@@ -167,7 +167,13 @@ int gemm_plan(const lithos_op_t& op, OpPlan* plan)
         // Four wavefronts gain 15 % in the loop and lose in an epilogue, 5 us a tile with bias and residual and 13 with GELU (us, four /
         // eight wavefronts: 2048 x 2048 x 512 with bias 24 / 18, with residual too 36 / 25, with GELU too 47 / 31; 4096 x 4096 x 1024 with
         // bias and residual 55 / 44; with all three 4096 x 8192 x 4096 284 / 265, 256 x 256 x 8192 167 / 165).
-        if (tile == 256 && K % 64 == 0) variant = long_rows || !pieces || (op.flags & (LITHOS_F_BIAS | LITHOS_F_GELU | LITHOS_F_RESIDUAL)) ? V_LDS256W8 : V_LDS256;
+        // Whole bf16 tiles of a short K, too: four wavefronts take 1.3 us longer in prologue and stores (1024 x 1024 x 64 8.2 / 6.9, x 256
+        // 11.2 / 10.3, x 512 15.1 / 15.0).  Tiles that reach beyond the matrix leave element by element from eight (1000 x 1000 x 64
+        // fp32 10.4 / 35), and more than a tile per CU of the chip hide more of it (8192 x 8192 x 256 TN 50 / 56, 8192 x 4096 x 128 NN on
+        // 64 CUs 68 / 58).
+        const bool short_whole = K <= ((M / 256) * (N / 256) < 256 ? 384 : 192) && M % 256 == 0 && N % 256 == 0 && !(op.flags & LITHOS_F_OUT_F32);
+        if (tile == 256 && K % 64 == 0)
+            variant = long_rows || !pieces || short_whole || (op.flags & (LITHOS_F_BIAS | LITHOS_F_GELU | LITHOS_F_RESIDUAL)) ? V_LDS256W8 : V_LDS256;
         if (tile == 128) {
             // V_MID128's k-tiles are 32 deep: 64 bytes, half a line, of a row of a k-contiguous operand.  With several workgroups on a CU
             // the line has left the L1 when its other half is fetched, a k-tile later.  V_MID128_PAIR fetches both halves in one turn,

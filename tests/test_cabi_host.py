@@ -116,6 +116,20 @@ def test_tile_of_a_split_gemm_that_names_none(m, n, k, tb, grid):
     assert _kernel(gemm(m, n, k, tb=tb, a_split=True))[1] == grid + (1,)
 
 
+@pytest.mark.parametrize("m,n,k,f32,pad,epi,kernel", [
+    (512, 256, 384, False, 0, False, LDS256W8), (512, 256, 448, False, 0, False, LDS256),       # whole bf16 tiles of a short K
+    (4096, 4096, 192, False, 0, False, LDS256W8), (4096, 4096, 256, False, 0, False, LDS256), (4096, 3840, 256, False, 0, False, LDS256W8),
+    (512, 264, 64, False, 0, False, LDS256), (504, 256, 64, False, 0, False, LDS256), (512, 256, 64, True, 0, False, LDS256),
+    (512, 256, 1024, False, 0, True, LDS256W8), (512, 256, 1024, False, 4, False, LDS256W8),    # epilogue, rows without 16-byte pieces
+])
+@pytest.mark.parametrize("ta,tb", [(False, False), (False, True), (True, False), (True, True)])
+def test_wavefronts_of_the_256_tile(ta, tb, m, n, k, f32, pad, epi, kernel):
+    op = gemm(m, n, k, ta=ta, tb=tb, tile=256, ldc=n + pad, bias=32768 if epi else None)
+    if f32:
+        op.flags |= B.F_OUT_F32
+    assert _kernel(op)[0] == kernel
+
+
 def _declared_symbols():
     text = open(os.path.join(ROOT, "include", "lithos.h")).read()
     text = re.sub(r"/\*.*?\*/", "", text, flags=re.S)
