@@ -250,7 +250,9 @@ int lithos_gemm_split_hint(const lithos_op_t* op, int32_t n_cus, int32_t* tile_o
  * grid {0,0,0} = use lithos_op_grid's; otherwise it must have the same total
  * (else LITHOS_EINVAL).  Atoms are ranges of the linear index, which every
  * factorisation of that total numbers alike, so a caller's grid only has to
- * agree in its total: the operator keeps its own tile geometry.
+ * agree in its total: the operator keeps its own tile geometry.  (A GEMM with
+ * SPLIT_A that names no tile also takes the total of its 128 tiles, or of its
+ * 64 tiles where the former are fewer than 128, and runs in those.)
  * part NULL = an unmasked queue.  stream (hipStream_t, may be NULL = none):
  * the first atom waits for work already queued on it and it waits for the
  * last atom, so the caller's own stream work orders with the launch, and

@@ -38,6 +38,7 @@ struct OpPlan {
 
 // Each operator family: validate + plan (no launch), and launch one atom.
 int gemm_plan(const lithos_op_t& op, OpPlan* plan);
+int gemm_square_tile(const lithos_op_t& op);     // of 64 and 128, by the number of tiles
 int gemm_launch(const lithos_op_t& op, const OpPlan& plan, const AtomArgs& atom, hipStream_t s);
 int rowops_plan(const lithos_op_t& op, OpPlan* plan);
 int rowops_launch(const lithos_op_t& op, const OpPlan& plan, const AtomArgs& atom, hipStream_t s);

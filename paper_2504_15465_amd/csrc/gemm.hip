@@ -60,6 +60,8 @@ static int auto_tile(int64_t M, int64_t N, bool tb, bool split, bool sliced, boo
     return !split && blocks(256, 256) >= 256 ? 256 : 128;
 }
 
+int gemm_square_tile(const lithos_op_t& op) { return ((op.dim[0] + 127) / 128) * ((op.dim[1] + 127) / 128) >= 128 ? 128 : 64; }
+
 static int tile_threads(int variant) { return variant == V_TILE64 || variant == V_TILE128 || variant == V_MID128 || variant == V_MID128_PAIR || variant == V_MID192 || variant == V_THIN || variant == V_LDS256 ? 256 : 512; }
 
 // full bf16 tiles can leave through LDS when whole 16-byte pieces of C rows are addressable

@@ -521,6 +521,12 @@ int lithos_launch_atomized(lithos_ctx_t* ctx, const lithos_op_t* op, lithos_dim3
         // same order for every factorisation: only the total has to agree.  The operator's own
         // grid (tile geometry, K slices on z) is what the kernels un-flatten that index with.
         uint64_t t = (uint64_t)grid.x * grid.y * grid.z;
+        if (t != plan.total && op->kind == LITHOS_OP_GEMM && op->tile == 0 && (op->flags & LITHOS_F_SPLIT_A)) {
+            // a split A that names no tile, in a grid of square tiles where the library would take another shape
+            lithos_op_t square = *op;
+            square.tile = gemm_square_tile(*op);
+            if ((rc = op_plan(square, &plan)) != LITHOS_OK) return rc;
+        }
         if (t != plan.total) return fail(LITHOS_EINVAL, "lithos_launch_atomized: grid has %llu blocks, the operator has %u", (unsigned long long)t, plan.total);
     }
     if ((rc = check_counters(ctx, plan)) != LITHOS_OK) return rc;

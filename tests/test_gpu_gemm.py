@@ -639,6 +639,38 @@ def test_callers_grid_of_the_same_total_changes_nothing(grid):
     assert e.value.code == B.EINVAL
 
 
+@pytest.mark.parametrize("m,n,k,square", [(128, 768, 200, (12, 2, 1)), (520, 3080, 136, (49, 9, 1)), (2048, 2304, 200, (18, 16, 1))])
+def test_callers_grid_of_square_tiles_for_a_split_gemm_that_names_none(m, n, k, square):
+    """32x64 and 64x192 tiles are the library's own choice: a caller's grid of the 64 or 128 tiles that such a GEMM is cut into
+    otherwise is taken at its word, whole and in atoms, and every block runs once; any other total is refused."""
+    a_bits, b_bits = inputs.gemm_operands(m, n, k, seed=8)
+    a = dev_bits(a_bits)
+    a = torch.stack([a, (a.float() * 2.0 ** -8).to(torch.bfloat16)]).contiguous()
+    b, ref = dev_bits(b_bits), O.gemm(a_bits, b_bits) * (1.0 + 2.0 ** -8)
+    c = nan_like((3, m, n), torch.float32)
+    ops = [B.gemm_op(a, b, c[i], m, n, k, a_split=True) for i in range(3)]
+    grid, _ = B.lithos_op_grid(ctx(), ops[0])
+    total = square[0] * square[1]
+    assert grid[0] * grid[1] != total
+    cnt = counters(total)
+    torch.cuda.synchronize()
+    B.lithos_launch_atomized(ctx(), ops[0], grid)
+    B.lithos_launch_atomized(ctx(), ops[1], square)
+    B.lithos_partition_sync(ctx(), None)
+    B.lithos_debug_block_counters(ctx(), cnt)
+    try:
+        B.lithos_launch_atomized(ctx(), ops[2], (total, 1, 1), 7)
+        B.lithos_partition_sync(ctx(), None)
+    finally:
+        B.lithos_debug_block_counters(ctx(), None)
+    assert cnt.cpu().tolist() == [1] * total
+    assert all(rel_fro(c[i], ref) <= 1e-6 for i in range(3)) and bits_equal(c[1], c[2])
+    for other in ((total + 1, 1, 1), (grid[0], grid[1], 2)):
+        with pytest.raises(B.LithosError) as e:
+            B.lithos_launch_atomized(ctx(), ops[0], other)
+        assert e.value.code == B.EINVAL
+
+
 def test_k_sliced_gemm_keeps_its_slices_under_a_callers_grid():
     """The K slices live on the operator's z axis; a caller's flat grid of the same total must not lose them."""
     m, n, k, S = 256, 256, 1024, 2
