@@ -175,15 +175,6 @@ __device__ __forceinline__ void unpack_bf16x8(const uint4& u, float* f)
     f[6] = __uint_as_float(u.w << 16); f[7] = __uint_as_float(u.w & 0xffff0000u);
 }
 
-__device__ __forceinline__ void dec_wave_lds_sync()
-{
-    // LDS operations of one wavefront complete in order; this only stops the compiler
-    // from moving reads of other lanes' data across the writes
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
-
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 
 // 16-byte slot of chunk c of key row r in a wavefront's key tile: the 8 lanes that read one chunk
@@ -262,7 +253,7 @@ __global__ __launch_bounds__(256, 3) void attn_dec_kernel(AttnArgs a, AtomArgs a
         }
 #pragma unroll
         for (int i = 0; i < R; ++i) kt[dec_kslot(4 * i + rg, c)] = kx[i];
-        dec_wave_lds_sync();
+        wave_lds_sync();
 
         float s8[8];
 #pragma unroll
@@ -300,7 +291,7 @@ __global__ __launch_bounds__(256, 3) void attn_dec_kernel(AttnArgs a, AtomArgs a
         l = l * corr + ls;
         m = nm;
         if (lane < G) cbuf[wave][lane] = corr;
-        dec_wave_lds_sync();
+        wave_lds_sync();
 
         float cr[G];
 #pragma unroll
@@ -320,7 +311,7 @@ __global__ __launch_bounds__(256, 3) void attn_dec_kernel(AttnArgs a, AtomArgs a
 #pragma unroll
                 for (int e = 0; e < 8; ++e) acc[h][e] += ph[h] * vf[e];
         }
-        dec_wave_lds_sync();                                       // the next unit rewrites the tile and p
+        wave_lds_sync();                                       // the next unit rewrites the tile and p
     }
 
     // merge the 16 partial softmaxes (wavefront-major, then row group) in that order: a wavefront's

@@ -83,6 +83,15 @@ __device__ __forceinline__ uint16_t f32_to_bf16(float f) { return (uint16_t)pack
 
 __device__ __forceinline__ float bf16_to_f32(uint16_t h) { return __uint_as_float((uint32_t)h << 16); }
 
+__device__ __forceinline__ void wave_lds_sync()
+{
+    // LDS operations of one wavefront complete in order; this only stops the compiler
+    // from moving reads of other lanes' data across the writes
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
 // GELU u * Phi(u).  |u| < 1.25: Phi = 1/2 + u P(u^2), 1.2e-8 of Phi(-|u|) at worst.  Beyond: max(u, 0) - |u| Phi(-|u|), where
 // |u| Phi(-|u|) = exp(-u^2 / 2) R(t) with t = 1 / (1 + 0.3 |u|), 2.3e-8 relative up to |u| = 14, where the exponential leaves
 // the normal numbers.  (Both fitted by iteratively reweighted least squares in float64, the coefficients rounded one after

@@ -115,15 +115,6 @@ __device__ __forceinline__ void epilogue_store_block(const GemmArgs& g, int m, i
     }
 }
 
-__device__ __forceinline__ void wave_lds_sync()
-{
-    // LDS operations of one wavefront complete in order; this only stops the compiler
-    // from moving reads of other lanes' data across the writes
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
-
 // ---- epilogue of a full bf16 tile through LDS ---------------------------------
 // Storing accumulators one element at a time costs a 2-byte global store per
 // element (1024 wavefront-wide stores for a 256x256 tile, ~25 us: as long as 14

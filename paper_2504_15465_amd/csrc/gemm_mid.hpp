@@ -16,18 +16,18 @@ namespace lithos {
 //
 // Against 32x32x16 MFMAs whose loads took five vector instructions each (us): 2048^3 NN 30 -> 21, 1536 x 1536 x 8192 TN 88 ->
 // 51, 1003 x 3000 x 1160 NT with epilogue 26.5 -> 23, split 4096 x 2304 x 768 41 -> 31, 4096 x 768 x 3072 55 -> 39.
-template <int BM, int BN, int WGM, int WGN, int S, int MINW, bool KSA, bool KSB, bool SPLIT>
-__global__ __launch_bounds__(256, MINW)
+template <int BM, int BN, int S, bool KSA, bool KSB, bool SPLIT>
+__global__ __launch_bounds__(256, 2)
 void gemm_mid_kernel(GemmArgs g, AtomArgs atom)
 {
 #ifdef __HIP_DEVICE_COMPILE__       // the buffer types exist on the device only
-    static_assert(WGM * WGN == 4 && S >= 3 && S <= 5, "built forms");
+    static_assert(S >= 3 && S <= 5, "built forms");
     constexpr bool PAIR = S == 5;                                        // k-tiles are fetched two at a time
-    constexpr int BK = 32, WM = BM / WGM, WN = BN / WGN, MI = WM / 16, NI = WN / 16, AP = SPLIT ? 2 : 1;
+    constexpr int BK = 32, WM = BM / 2, WN = BN / 2, MI = WM / 16, NI = WN / 16, AP = SPLIT ? 2 : 1;
     constexpr int NF = AP * MI + NI, NM = AP * MI * NI;                  // fragments and MFMAs of a k-tile
     constexpr int TA = BM / 16, TB = BN / 16;                            // 1 KB blocks of an operand's k-tile
-    constexpr int NA = TA / 4, NB = (TB + 3) / 4, NL = AP * NA + NB;     // .. that a wavefront fetches
-    static_assert(TA % 4 == 0 && (S - 1) * NL < 64, "loads");
+    constexpr int NA = TA / 4, NB = TB / 4, NL = AP * NA + NB;     // .. that a wavefront fetches
+    static_assert(TA % 4 == 0 && TB % 4 == 0 && (S - 1) * NL < 64, "loads");
     // separate arrays, each addressed statically: the compiler can then tell that the LDS reads of one stage do
     // not depend on the loads in flight into another
     __shared__ __attribute__((aligned(1024))) uint16_t A0[AP * BM * BK];
@@ -57,7 +57,7 @@ void gemm_mid_kernel(GemmArgs g, AtomArgs atom)
     const uint32_t z = __builtin_amdgcn_readfirstlane(blk.z);
     const int tid = threadIdx.x, lane = tid & 63, l16 = lane & 15, quad = lane >> 4;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int wm = wave / WGN, wn = wave % WGN;
+    const int wm = wave >> 1, wn = wave & 1;
     int ks0, ks1;                                   // this block's k range is [klo, klo + to_fetch)
     slice_ktiles(g, z, (g.K + 63) / 64, ks0, ks1);
     const int64_t klo = __builtin_amdgcn_readfirstlane(ks0) * 64;
@@ -87,7 +87,9 @@ void gemm_mid_kernel(GemmArgs g, AtomArgs atom)
     constexpr std::bool_constant<KSB> ksb{};
     constexpr std::integral_constant<int, BM> rows_a{};
     constexpr std::integral_constant<int, BN> rows_b{};
-    const auto b_block = [&](int i) __attribute__((always_inline)) { return min(wave * NB + i, TB - 1); };   // the last one again where they do not divide
+    // The bound is never reached: without it the compiler keeps more addresses in registers (181 against 158 with B k-strided) and
+    // 2048 x 2048 x 256 NN on 192 CUs takes 8.9 us instead of 8.5.
+    const auto b_block = [&](int i) __attribute__((always_inline)) { return min(wave * NB + i, TB - 1); };
     uint32_t oa[NA], ob[NB];
 #pragma unroll
     for (int i = 0; i < NA; ++i) oa[i] = lane_off(ksa, rows_a, (int)g.lda, m0, g.M, wave * NA + i);
@@ -218,13 +220,11 @@ void gemm_mid_kernel(GemmArgs g, AtomArgs atom)
     static_for<U - 1>([&](auto t) __attribute__((always_inline)) { if (it + decltype(t)::value < n_it) tile_step(t); });
     turn(std::integral_constant<int, 0>{});         // the stages are free
 
-    // a strip is 32 WN elements of LDS as floats: one of A's stages or, with at least four of them, of B's for each wavefront
-    constexpr bool FROM_B = S >= 4 && BN >= AP * BM;
-    constexpr int ROOM = (FROM_B ? BN * BK : S >= 4 ? AP * BM * BK : (AP * BM < BN ? AP * BM : BN) * BK) / (32 * WN), D = ROOM >= MI ? MI : ROOM >= 2 ? 2 : 1;
+    // Strips, 32 WN elements of LDS each as floats: a stage of B for each wavefront, of three stages two of either operand.
+    constexpr int ROOM = (S > 3 || BN < AP * BM ? BN : AP * BM) * BK / (32 * WN), D = ROOM >= MI ? MI : ROOM >= 2 ? 2 : 1;
     static_assert(ROOM >= 1 && MI % D == 0, "a strip in one stage of an operand");
     uint16_t* scratch;
-    if constexpr (FROM_B) scratch = wave == 0 ? B0 : wave == 1 ? B1 : wave == 2 ? B2 : B3;
-    else if constexpr (S >= 4) scratch = wave == 0 ? A0 : wave == 1 ? A1 : wave == 2 ? A2 : A3;
+    if constexpr (S > 3) scratch = wave == 0 ? B0 : wave == 1 ? B1 : wave == 2 ? B2 : B3;
     else scratch = wave == 0 ? A0 : wave == 1 ? A1 : wave == 2 ? B0 : B1;
     epilogue16<D>(g, acc, mw, nw, lane, whole, scratch);
 #endif

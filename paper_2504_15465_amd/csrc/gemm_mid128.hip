@@ -5,9 +5,9 @@
 namespace lithos {
 
 template <int S, bool KSA, bool KSB>
-static gemm_fn plain() { return (gemm_fn)gemm_mid_kernel<128, 128, 2, 2, S, 2, KSA, KSB, false>; }
+static gemm_fn plain() { return (gemm_fn)gemm_mid_kernel<128, 128, S, KSA, KSB, false>; }
 template <bool KSB>
-static gemm_fn split_a() { return (gemm_fn)gemm_mid_kernel<128, 128, 2, 2, 3, 2, false, KSB, true>; }
+static gemm_fn split_a() { return (gemm_fn)gemm_mid_kernel<128, 128, 3, false, KSB, true>; }
 
 gemm_fn gemm_mid128_fn(bool ta, bool tb, bool split)
 {

@@ -5,7 +5,7 @@ namespace lithos {
 
 gemm_fn gemm_mid192_fn(bool tb)
 {
-    return tb ? (gemm_fn)gemm_mid_kernel<64, 192, 2, 2, 3, 2, false, false, true> : (gemm_fn)gemm_mid_kernel<64, 192, 2, 2, 3, 2, false, true, true>;
+    return tb ? (gemm_fn)gemm_mid_kernel<64, 192, 3, false, false, true> : (gemm_fn)gemm_mid_kernel<64, 192, 3, false, true, true>;
 }
 
 } // namespace lithos
