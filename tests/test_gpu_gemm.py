@@ -72,8 +72,8 @@ def test_tiles_layouts_ragged_shapes(tile, ta, tb):
 
 @pytest.mark.parametrize("m,n,k", [(520, 776, 320), (256, 256, 64), (300, 260, 128), (1, 8, 192)])
 def test_nt_256_tile_with_k_multiple_of_64(m, n, k):
-    """A [M,K] times B [N,K] with 256x256 tiles and K % 64 == 0 takes the kernel that loads
-    global memory straight into LDS: odd and even numbers of k-tiles, ragged M and N."""
+    """A [M,K] times B [N,K] with 256x256 tiles and K % 64 == 0 takes the kernels that load global memory straight into
+    LDS (four wavefronts, or eight where rows of C are not whole 16-byte pieces): odd and even numbers of k-tiles, ragged M and N."""
     a_bits, b_bits = inputs.gemm_operands(m, n, k, seed=77, tb=True)
     ref = O.gemm(a_bits, b_bits, tb=True)
     c_full, grid, _ = run_gemm(a_bits, b_bits, m, n, k, False, True, 256)
@@ -596,7 +596,7 @@ def test_training_shapes_full_size_sampled_rows():
 @pytest.mark.parametrize("tile,k", [(128, 320), (256, 320), (256, 264)])
 def test_split_bf16_output_of_plain_bf16_gemm(tile, k):
     """C written as a hi + lo bf16 pair by the kernels that take ordinary bf16 operands (through LDS in two
-    passes where the kernel has that path; of the 256 tiles the ragged ones element by element): the hi plane is the
+    passes; of the 256 tiles with another K than multiples of 64 the ragged ones element by element): the hi plane is the
     single-plane result bit for bit, hi + lo carries ~16 significant bits."""
     m, n = 520, 776
     a_bits, b_bits = inputs.gemm_operands(m, n, k, seed=61)
@@ -966,3 +966,68 @@ def test_rows_without_wide_stores_in_every_layout(tile, ta, tb, split, k):
                 if pair:
                     both = got.double() + c[1, :, :n].double()
                     assert np.abs(both.cpu().numpy() - ref).max() <= 2.0 ** -16 * np.abs(ref).max() + bound
+
+
+@pytest.mark.parametrize("ta,tb", [(False, False), (False, True), (True, False), (True, True)])
+@pytest.mark.parametrize("k", [64, 192, 448])
+def test_256_tile_in_every_layout_within_padding(ta, tb, k):
+    """256 tiles with K a multiple of 64, in the middle and at the last row and column of a tile, operands and C inside larger buffers of NaN:
+    plain (four wavefronts; the whole tiles of a short K eight) and with bias, GELU and residual (eight); fp32, bf16 and paired
+    bf16 C, whole and in atoms.
+    fp32 sums: at most K * 2^-24 of the sum of magnitudes (K / 4 for uniform operands), GELU steepens that by at most 1.13."""
+    for m, n in ((264, 280), (256, 512)):
+        a_bits, b_bits = inputs.gemm_operands(m, n, k, seed=k + m, ta=ta, tb=tb)
+        lda, ldb, ldc = a_bits.shape[1] + 8, b_bits.shape[1] + 16, n + 8
+        a, b = _padded(a_bits, lda), _padded(b_bits, ldb)
+        acc = O.gemm(a_bits, b_bits, ta=ta, tb=tb)
+        bias, resid = inputs.normal_f32((n,), 90), inputs.normal_f32((m, n), 91)
+        full = O.bias_act(acc, bias, gelu=True) + resid
+        epi_kw = dict(bias=torch.from_numpy(bias).cuda(), gelu=True, residual=torch.from_numpy(resid).cuda())
+        bound = 1.13 * (2.0 ** -24 * k * (k / 4 + 1) + 2.0 ** -19)
+        for epi, ref in ((dict(), acc), (epi_kw, full)):
+            for dt, pair in ((torch.float32, False), (torch.bfloat16, False), (torch.bfloat16, True)):
+                outs = []
+                for atom_blocks in (0, 1):
+                    c = nan_like((2 if pair else 1, m + 1, ldc), dt)
+                    op = B.gemm_op(a, b, c, m, n, k, ta=ta, tb=tb, tile=256, lda=lda, ldb=ldb, ldc=ldc, c_split=pair, **epi)
+                    op.dim[4] = (m + 1) * ldc if pair else 0        # the planes with a row of padding each
+                    _launch(op, atom_blocks)
+                    assert torch.isnan(c[:, m].float()).all() and torch.isnan(c[:, :, n:].float()).all()
+                    assert not torch.isnan(c[:, :m, :n].float()).any()
+                    outs.append(c)
+                assert bits_equal(outs[0], outs[1])
+                got = outs[0][0, :m, :n]
+                if dt is torch.float32:
+                    assert np.abs(got.double().cpu().numpy() - ref).max() <= bound
+                else:
+                    bf16_close(got, ref, abs_tol=bound)
+                    if pair:
+                        both = got.double() + outs[0][1, :m, :n].double()
+                        assert np.abs(both.cpu().numpy() - ref).max() <= 2.0 ** -16 * np.abs(ref).max() + bound
+
+
+@pytest.mark.parametrize("m,n,k,tb,slices,grid", [
+    (2048, 768, 448, False, 3, (4, 32, 3)),     # 64x192 tiles, an uneven cut of seven k-tiles
+    (1100, 1500, 200, True, 4, (8, 18, 4)),     # ragged, one k-tile of 64 to a slice and the last of 8
+    (2048, 2304, 136, False, 2, (12, 32, 2)),
+    (100, 200, 520, True, 5, (4, 2, 5)),        # few tiles: 64x64 (32x64 ones take no slices)
+])
+def test_split_activations_in_k_slices_of_tiles_chosen_by_size(m, n, k, tb, slices, grid):
+    """Every plane of a K-sliced split GEMM that names no tile is the product over its range of 64-deep k-tiles, the same in any atoms."""
+    a_bits, b_bits = inputs.gemm_operands(m, n, k, seed=slices, tb=tb)
+    a = dev_bits(a_bits)
+    a = torch.stack([a, (a.float() * 2.0 ** -8).to(torch.bfloat16)]).contiguous()
+    b = dev_bits(b_bits)
+    outs = []
+    for atom_blocks in (0, 50):
+        c = nan_like((slices, m, n), torch.float32)
+        op = B.gemm_op(a, b, c, m, n, k, tb=tb, a_split=True, k_slices=slices)
+        assert B.lithos_op_grid(ctx(), op)[0] == grid
+        _launch(op, atom_blocks)
+        outs.append(c)
+    assert bits_equal(outs[0], outs[1])
+    tiles = (k + 63) // 64
+    for z in range(slices):
+        lo, hi = z * tiles // slices * 64, min(k, (z + 1) * tiles // slices * 64)
+        ref = O.gemm(a_bits[:, lo:hi], b_bits[:, lo:hi] if tb else b_bits[lo:hi], tb=tb) * (1.0 + 2.0 ** -8)
+        assert np.abs(outs[0][z].double().cpu().numpy() - ref).max() <= 2.0 ** -24 * (hi - lo) * ((hi - lo) / 4 + 1)
