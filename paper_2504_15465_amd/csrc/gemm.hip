@@ -52,9 +52,10 @@ static int auto_tile(int64_t M, int64_t N, bool tb, bool split, bool sliced, boo
         const int64_t n64 = blocks(64, 64), n192 = blocks(64, 192);
         if (n128 < 128) return n192 >= 128 && n64 > 256 ? TILE_64X192 : 64;
         // Else against 128x128, by the area of the busiest CU's tiles and of all (us, 64x192 / 128x128: 4096 x 768 x 3072 36 / 43, 4096 x
-        // 2304 x 768 31 / 37; 1500 x 2304 x 3072 62 / 47, 8192 x 256 x 768 on 64 CUs 35 / 27); not with half lines of two operands, of
-        // which the narrower tile fetches more (2048 x 2048 x 2056 NT 66 / 50).
-        return (lines || !tb) && rounds(n192) * 3 < rounds(n128) * 4 && n192 * 3 <= n128 * 4 ? TILE_64X192 : 128;
+        // 2304 x 768 31 / 37, 1500 x 2304 x 3072 62 / 47, 8192 x 256 x 768 on 64 CUs 35 / 27; as much area in 4096 x 3072 x 768 48.6 / 48.2, and
+        // the encoder of 4096 tokens 0.6 % faster); not with half lines of two operands, of which the narrower tile fetches more
+        // (2048 x 2048 x 2056 NT 66 / 50).
+        return (lines || !tb) && rounds(n192) * 3 <= rounds(n128) * 4 && n192 * 3 <= n128 * 4 ? TILE_64X192 : 128;
     }
     if (n128 < 128) return 64;
     return !split && blocks(256, 256) >= 256 ? 256 : 128;

@@ -107,7 +107,7 @@ def test_depth_of_the_128_tiles_k_tiles(ta, tb, m, n, k, pad, kernel):
     (2048, 768, 768, False, (4, 32)),           # 384 of them: 128 of 64x192
     (4096, 768, 3072, False, (4, 64)),          # 256 of 64x192, one round, against 192 of 128x128
     (4096, 2304, 768, True, (12, 64)),
-    (4096, 3072, 768, False, (24, 32)),         # as much area on the busiest CU: 128x128
+    (4096, 3072, 768, False, (16, 64)),         # as much area on the busiest CU and in all
     (1536, 2304, 768, False, (18, 12)),         # 288 of 64x192, two rounds, against 216 of 128x128
     (8192, 256, 768, False, (2, 64)),           # a third of 64x192 tiles' columns would be padding
     (4096, 768, 776, False, (4, 64)), (4096, 768, 776, True, (6, 32)),      # two operands whose rows do not begin on lines
