@@ -47,8 +47,8 @@ HBM_PEAK_GBS = 8000.0
 # HBM bytes per whole 8192^3 launch, by GEMM tile: rocprofv3 --pmc FETCH_SIZE and WRITE_SIZE (KiB per dispatch),
 # each scaled by what the same counter reads for a 1 GiB device-to-device copy (fetch x 2.00, write x 1.00).
 # Source: profiles/gemm_lds256_8192_and_cfg2_stacking.md, section 3 (256 tiles: 786859 KiB x 2 + 131072 KiB), and
-# profiles/tile_gemms_and_encoder.md (128 tiles: 1731207 KiB x 2 + 131072 KiB).
-TRAFFIC_BYTES = {256: 1.75e9, 128: 3.68e9}
+# profiles/tile_gemms_and_encoder.md (128 tiles: 1620927 KiB x 2 + 131072 KiB).
+TRAFFIC_BYTES = {256: 1.75e9, 128: 3.45e9}
 ALGORITHMIC_BYTES_8192 = 3 * 8192 * 8192 * 2.0      # A and B read once, C written once, bf16
 TAIL_REQUESTS, TAIL_WARMUP = 2000, 100              # fixed-size legs behind "tail_study" (p99 needs samples)
 TAIL_REQUESTS_LONG, TAIL_WARMUP_LONG = 5000, 200    # the two legs whose tails are compared: static masks, full scheduler

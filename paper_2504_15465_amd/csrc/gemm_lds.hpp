@@ -41,8 +41,8 @@ constexpr int wait_imm(int n) { return (n & 15) | 0x70 | ((n >> 4) << 14); }
 // Bound by the latency of the chain of k-tiles: what a k-tile brings is new to the die's L2, about 0.65 us a tile for grids of
 // a few blocks whatever the number of stages.  Against the form that staged through registers into one buffer 512^3 in eight
 // atoms on 32 CUs 55 -> 41 us.  Larger tiles, and a split A in grids of more or fewer tiles, are gemm_mid_kernel's and
-// gemm_thin_kernel's; 128 tiles of two k-contiguous operands with a long K stay here, whose 64-deep k-tiles read whole
-// 128-byte lines.
+// gemm_thin_kernel's; here stay 128 tiles of rows that need 64-bit addresses, and of two k-contiguous operands with a long K
+// and many tiles, whose lines 64-deep k-tiles read whole (see gemm_plan).
 template <int BM, int BN, int WGM, int WGN, int KG, int BK, int S, int MINW, bool TA, bool TB, bool SPLIT, bool ST>
 __global__ __launch_bounds__(WGM * WGN * KG * 64, MINW)
 void gemm_lds_kernel(GemmArgs g, AtomArgs atom)

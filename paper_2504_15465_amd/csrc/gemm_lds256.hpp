@@ -7,8 +7,9 @@ namespace lithos {
 // Four wavefronts of 128x128, one per SIMD: 256 accumulator registers and 256 for the rest.
 //
 // What bounds it: on random data the chip lowers its clock with the power that the MFMAs and everything around them
-// take (8192^3: 2.39 GHz on zeros, 1.55 to 1.9 on random data, the more the busier the MFMA pipes), so a kernel that
-// only fills the pipes better gains little, and one that does less beside the MFMAs gains twice.  Hence
+// take (8192^3: 2.39 GHz on zeros; on random data 1.8 for a loop with the MFMA pipes 62 % busy, 1.55 for one of the same
+// MFMAs and 81 %, 1.84 for this one and 79 %), so a kernel that only fills the pipes better gains little, and one that does
+// less beside the MFMAs gains twice.  Hence
 //  * 128x128 per wavefront: 8 + 8 KB of LDS reads for 64 MFMAs; 128x64 reads half as much again;
 //  * v_mfma_f32_16x16x32_bf16: per multiplication it moves half the accumulators of the 32x32x16 form, and twice the
 //    operands, 0.5 bytes against 0.625: 8192^3 NN 735 us against 773;

@@ -7,8 +7,8 @@
 // 16.8 with 64x64 tiles (24 tiles, two groups of wavefronts), 128 x 1024 x 1024 7.1 against 8.5, 128 x 768 x 768 6.3 against 7.4.
 // Made for partitions of a quarter of the chip or more: where CUs are fewer than about 1.3 times the tiles some get two, one after
 // the other, and 64x64 tiles are faster (128 x 768 x 768 10.9 / 7.5 on 24 to 48 CUs, 15.6 / 10.9 on 16, 29 / 15.5 on 8); a grid cannot
-// depend on the partition.  Two workgroups per CU (64 KB of LDS, the fragments of A loaded into registers) help neither: 30 against
-// 22 for K = 3072 on 48 CUs, 17.0 against 12.4 on 64, twice the requests of A to a CU's L1 taking longer than the round trips.
+// depend on the partition.  Two workgroups per CU (64 KB of LDS, the fragments of A loaded into registers) help neither: K = 3072 takes
+// 30 us against 22 on 48 CUs and 17.0 against 12.4 on 64.
 // The same for plain operands in 64x64 tiles is slower up to K = 4096 (512^3 6.6 / 5.3, 512 x 512 x 4096 17.0 / 16.0).
 #include "gemm_mfma16.hpp"
 

@@ -1,4 +1,4 @@
-"""The benchmark command exactly as the harness runs it at the end of a round: it must exit 0 and print
+"""The default benchmark command as a user runs it: it must exit 0 and print
 one JSON line with the contract's keys (this is the command that an index error once stopped)."""
 import json
 import os
